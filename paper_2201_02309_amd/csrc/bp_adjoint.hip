@@ -24,29 +24,33 @@ using namespace bpdev;
 // several times faster here than its float32 one, and exact enough that the flushed float32
 // sums round once.  Group words are bytes while the groups fit in 4 bits, so that the
 // double-buffered boxes still leave room for four workgroups per CU.
-constexpr int kLPT = kLP;         // box columns
-// LDS row pitch of the boxes (doubles): 64 would put a column's cells of every row in one
-// bank pair, so lanes scattering to one column at different rows would conflict; 66 moves
-// each row by four banks (65, 68, 70, 72 and 80 were slower).  The hull's word table is
-// sized so that a 16-slice workgroup still takes exactly 40960 bytes, four per CU: views
-// of hulls up to 1784 long (the largest hull of the 512^3 / 55296-view workload is 1649).
-// Whole adjoint against 64-double rows: clinical 512^2 x 128 workload 44.3 ms against
-// 56.8 ms, 16-row network window 2.82 against 3.30 ms, 184-column sparse detector 51.1
-// against 51.7 ms.
-constexpr int kRowT = 66;
+//
+// The boxes take the workgroup's dynamic LDS, sized by the plan's largest footprint box
+// (bpT_shape): rows of `pitch` accumulators, pitch = 2 (mod 32), so that a column's cells of
+// successive rows lie four banks apart (a multiple of 16 puts them in one bank pair, and lanes
+// scattering to one column at different rows conflict; 65, 68, 70, 72 and 80 were slower than 66).
+// With the tile fixed at 32 rows x 64 columns, plans with larger boxes scattered those views'
+// taps to HBM atomics; the kernel's time for the 256 x 256 x 64 sparse-detector workload, whose
+// boxes are 49 x 25 cells, went from 50.4 to 7.5 ms, and with 40 x 79 boxes (256 x 256 x 32,
+// 736 columns, fixed point) from 12.1 to 5.6 ms.  Words cover hulls up to kHullT views (the largest hull of the 512^3 /
+// 55296-view workload is 1649).
 constexpr int kHullT = 1784;
+constexpr unsigned kLdsBytes = 163840;    // per CU and workgroup on gfx950
+
+// One box buffer: rows x pitch accumulators.
+struct BpTShape {
+    int pitch, rows;
+};
 
 // DET: the deterministic mode's accumulators are 64-bit fixed point (integer adds are
 // associative, so the result does not depend on the order of the atomics).
 template <int KZ, bool DET>
-struct BpTShared {
+struct BpTTypes {
     static constexpr int NG = KZ / kKG;
     using Word = typename std::conditional<(NG <= 4), unsigned char, unsigned short>::type;
     using Acc = typename std::conditional<DET, unsigned long long, double>::type;
     static constexpr int kFull = NG <= 4 ? 4 : 8;
-    __attribute__((aligned(16))) Acc box[2][kRowT * lds_rows<KZ>()];
-    Word words[4][kHullT];
-    int red[8];
+    static constexpr unsigned kWordBytes = 4 * kHullT * sizeof(Word);
 };
 
 // v * S rounded to the nearest integer, two's complement (|v| S < 2^62 by the choice of S)
@@ -77,23 +81,25 @@ __device__ inline unsigned long long to_fixed(float v, double S) {
 // integer atomics); S = *fscale, a power of two chosen from max |fbar| so that no sum can
 // reach 2^62.  Integer sums do not depend on their order: the result is the same bits on
 // every run.
-template <int KZ, bool FB, bool DET>
+template <int KZ, bool FB, bool DET, int PITCH>
 __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *__restrict__ gFout,
                          const double *__restrict__ fscale, int rows, int cols, long long first_view,
                          const float4 *__restrict__ view_tab, const uint2 *__restrict__ box_tab,
-                         const float4 *__restrict__ ray_tab, int series, int bxi, int byi, int bz,
-                         BpTShared<KZ, DET> &S) {
-    using Acc = typename BpTShared<KZ, DET>::Acc;
+                         const float4 *__restrict__ ray_tab, int series, const BpTShape shape, int bxi,
+                         int byi, int bz, unsigned char *lds, int *red) {
+    using Acc = typename BpTTypes<KZ, DET>::Acc;
     typedef __attribute__((address_space(3))) Acc LdsAcc;
     float *gFbar = static_cast<float *>(gFout);
     unsigned long long *gFbar64 = static_cast<unsigned long long *>(gFout);
     const double fx = DET ? *fscale : 0.0;
     static_assert(KZ % kKG == 0 && KZ / kKG <= 8, "groups use 8-bit masks");
-    constexpr int kLR = lds_rows<KZ>();
     constexpr int NG = KZ / kKG;
-    auto &box = S.box;
-    auto &words = S.words;
-    auto &red = S.red;
+    using Word = typename BpTTypes<KZ, DET>::Word;
+    constexpr int kFull = BpTTypes<KZ, DET>::kFull;
+    const int pitch_a = PITCH ? PITCH : shape.pitch;
+    const int cells = pitch_a * shape.rows;                  // of one buffer
+    LdsAcc *box = (LdsAcc *)lds;
+    Word *words = reinterpret_cast<Word *>(lds + 2 * (size_t)cells * sizeof(Acc));
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
@@ -151,12 +157,10 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
         red[4 + wave] = whi;
     }
     // both box buffers start zeroed (every flush leaves its cells zero again)
-    for (int i = tid; i < 2 * kRowT * kLR; i += kNT) (&box[0][0])[i] = 0;
+    for (int i = tid; i < 2 * cells; i += kNT) box[i] = 0;
     __syncthreads();
     const int mlo = __builtin_amdgcn_readfirstlane(min(min(red[0], red[1]), min(red[2], red[3])));
     const int mhi = __builtin_amdgcn_readfirstlane(max(max(red[4], red[5]), max(red[6], red[7])));
-    using Word = typename BpTShared<KZ, DET>::Word;
-    constexpr int kFull = BpTShared<KZ, DET>::kFull;
     // (an empty hull, mlo = INT_MAX > mhi = INT_MIN, takes no words: mhi - mlo would overflow)
     const bool use_words = mlo <= mhi && mhi - mlo < kHullT;
     if (use_words) {
@@ -168,7 +172,7 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
                 if (m >= g_alo[g] && m <= g_ahi[g]) word |= 1u << g;
                 if (m >= g_flo[g] && m <= g_fhi[g]) word |= 1u << (kFull + g);
             }
-            words[wave][w] = (Word)word;
+            words[wave * kHullT + w] = (Word)word;
         }
     }
     __syncthreads();
@@ -181,24 +185,26 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
         box_tab + ((size_t)(run * p.tiles_y + byi) * p.tiles_x + bxi) * p.W;
     const float4 *__restrict__ rays = ray_tab + ((size_t)byi * p.tiles_x + bxi) * p.W;
     const size_t vstride = (size_t)rows * cols;
-    auto fits = [](const BpBox &b) { return !FB || (b.nr <= kLR && b.nc <= kLPT); };
-    // flush of view m's box from buffer buf: lanes over 4 rows x 64 columns per pass
+    auto fits = [&](const BpBox &b) { return !FB || (b.nr <= shape.rows && b.nc <= kBpBoxCols); };
+    // flush of view m's box from buffer buf: kFL lanes over a row per pass (cells of a row past
+    // the box are zero), wider boxes in blocks of kFL columns
+    constexpr int kFL = PITCH == 34 ? 32 : 64;
     auto flush = [&](int m, const BpBox &b, int buf) {
-        LdsAcc *bx = (LdsAcc *)box[buf];
+        LdsAcc *bx = box + buf * cells;
         const size_t vo = (size_t)(base + m - first_view) * vstride;
-        const int cc = tid & 63;
-        for (int rr = tid >> 6; rr < b.nr; rr += 4) {
-            LdsAcc *cell = bx + __mul24(rr, kRowT) + cc;
-            const Acc v = *cell;
-            if (v != 0) {
-                *cell = 0;
-                const int r = b.r0 + rr, c = b.c0 + cc;
-                if ((unsigned)r < (unsigned)rows && (unsigned)c < (unsigned)cols) {
-                    if constexpr (DET) atomicAdd(gFbar64 + vo + (size_t)r * cols + c, v);
-                    else atomicAdd(gFbar + vo + (size_t)r * cols + c, (float)v);
+        for (int cc = tid & (kFL - 1); cc < (PITCH ? kFL : (int)b.nc); cc += kFL)
+            for (int rr = tid / kFL; rr < b.nr; rr += kNT / kFL) {
+                LdsAcc *cell = bx + __mul24(rr, pitch_a) + cc;
+                const Acc v = *cell;
+                if (v != 0) {
+                    *cell = 0;
+                    const int r = b.r0 + rr, c = b.c0 + cc;
+                    if ((unsigned)r < (unsigned)rows && (unsigned)c < (unsigned)cols) {
+                        if constexpr (DET) atomicAdd(gFbar64 + vo + (size_t)r * cols + c, v);
+                        else atomicAdd(gFbar + vo + (size_t)r * cols + c, (float)v);
+                    }
                 }
             }
-        }
     };
     BpBox prev_b = unpack_box(ldg(boxes + (mlo <= mhi ? mlo : 0)));
     for (int m = mlo; m <= mhi; ++m) {
@@ -235,7 +241,7 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
         const float rmax = (float)(b.nr - 2);
         const float mf = (float)m;
         unsigned word = (1u << NG) - 1u;
-        if (use_words) word = __builtin_amdgcn_readfirstlane(words[wave][m - mlo]);
+        if (use_words) word = __builtin_amdgcn_readfirstlane(words[wave * kHullT + m - mlo]);
         // the view's active slices in register order: each slice adds its row weights to
         // two pending rows (R, R+1) kept in registers; a row's two taps (columns c0, c0+1)
         // are scattered once the walk has moved past it, so slices that share detector
@@ -271,11 +277,11 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
         };
         if (fits(b)) {
             // LDS addresses in 32 bits (the box is shared memory)
-            LdsAcc *bx = (LdsAcc *)box[buf] + c0;
+            LdsAcc *bx = box + buf * cells + c0;
             walk([&](int row, float v) {
                 if (v != 0.0f) {
                     const float v1 = v * tc;
-                    LdsAcc *cell = bx + __mul24(row, kRowT);
+                    LdsAcc *cell = bx + __mul24(row, pitch_a);
                     if constexpr (DET) {
                         const unsigned long long q = to_fixed(v, fx), q1 = to_fixed(v1, fx);
                         __hip_atomic_fetch_add(cell, q - q1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -316,17 +322,19 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
     if (mlo <= mhi && fits(prev_b)) flush(mhi, prev_b, (mhi - mlo) & 1);
 }
 
-template <int KZ, bool FB, bool DET>
+template <int KZ, bool FB, bool DET, int PITCH>
 __global__ __launch_bounds__(kNT) void k_bpT_lds(BpArgs p, const float *__restrict__ fvol,
                                                  void *__restrict__ gFout,
                                                  const double *__restrict__ fscale, int rows,
                                                  int cols, long long first_view,
                                                  const float4 *__restrict__ view_tab,
                                                  const uint2 *__restrict__ box_tab,
-                                                 const float4 *__restrict__ ray_tab, int series) {
-    __shared__ BpTShared<KZ, DET> S;
-    bpT_tile<KZ, FB, DET>(p, fvol, gFout, fscale, rows, cols, first_view, view_tab, box_tab, ray_tab, series,
-                          blockIdx.x, blockIdx.y, blockIdx.z, S);
+                                                 const float4 *__restrict__ ray_tab, int series,
+                                                 BpTShape shape) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    __shared__ int red[8];
+    bpT_tile<KZ, FB, DET, PITCH>(p, fvol, gFout, fscale, rows, cols, first_view, view_tab, box_tab, ray_tab, series,
+                          shape, blockIdx.x, blockIdx.y, blockIdx.z, lds, red);
 }
 
 // Whether the odd series serves every voxel's angle from its tile centre's ray: a voxel lies
@@ -347,17 +355,56 @@ int series_serves(const KParams &k) {
     return d > h && h <= 0.2 * std::sqrt(d * d - h * h) ? 1 : 0;
 }
 
+// Box buffers of a plan: its largest footprint box in rows of 34 or 66 accumulators (compiled
+// in) when it has at most 32 or 64 columns, else of 2 (mod 32) accumulators.  A plan whose
+// two buffers exceed the LDS takes the 32 x 64 tile and scatters the views with larger boxes
+// to HBM (fb): an LDS box, however large, is merged by the workgroup and written as whole rows,
+// while HBM atomics go one lane at a time.
 template <int KZ, bool DET>
-void launch_bpT(bool fb, dim3 grid, hipStream_t s, const BpArgs &a, const float *gvol, void *gFout,
-                const double *fscale, int rows, int cols, long long first_view, const float4 *view,
-                const uint2 *boxes, const float4 *rays, int series) {
-    // fb: HBM path for boxes beyond the LDS tile
-    if (fb)
-        hipLaunchKernelGGL((k_bpT_lds<KZ, true, DET>), grid, dim3(kNT), 0, s, a, gvol, gFout, fscale, rows,
-                           cols, first_view, view, boxes, rays, series);
-    else
-        hipLaunchKernelGGL((k_bpT_lds<KZ, false, DET>), grid, dim3(kNT), 0, s, a, gvol, gFout, fscale, rows,
-                           cols, first_view, view, boxes, rays, series);
+BpTShape bpT_shape(const KParams &k, bool &fb, unsigned &bytes) {
+    using T = BpTTypes<KZ, DET>;
+    auto size = [](const BpTShape &s) {
+        return 2u * (unsigned)s.pitch * (unsigned)s.rows * (unsigned)sizeof(typename T::Acc) + T::kWordBytes;
+    };
+    BpTShape s{};
+    s.pitch = ((k.bp_box_cols < 1 ? 1 : k.bp_box_cols) + 31) / 32 * 32 + 2;
+    s.rows = k.bp_box_rows < 2 ? 2 : k.bp_box_rows;
+    fb = (long long)s.pitch * s.rows > 16384 || size(s) + 64 > kLdsBytes;
+    if (fb) {
+        s.pitch = kBpBoxCols + 2;
+        s.rows = kBpBoxRows;
+    }
+    bytes = size(s);
+    return s;
+}
+
+template <int KZ, bool DET>
+void launch_bpT(const KParams &k, hipStream_t s, const float *gvol, void *gFout, const double *fscale) {
+    const dim3 grid((unsigned)k.bp_tiles_x, (unsigned)k.bp_tiles_y, (unsigned)(k.n_pitches * k.bp_runs));
+    const BpArgs a = bp_args(k);
+    const uint2 *boxes = reinterpret_cast<const uint2 *>(k.boxes);
+    const float4 *rays = reinterpret_cast<const float4 *>(k.tref);
+    const int series = series_serves(k);
+    bool fb;
+    unsigned bytes;
+    const BpTShape shape = bpT_shape<KZ, DET>(k, fb, bytes);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kNT), bytes, s, a, gvol, gFout, fscale, k.rows, k.cols, k.first_view,
+                           k.view, boxes, rays, series, shape);
+    };
+    if (fb) go(k_bpT_lds<KZ, true, DET, 66>);
+    else if (shape.pitch == 34) go(k_bpT_lds<KZ, false, DET, 34>);
+    else if (shape.pitch == 66) go(k_bpT_lds<KZ, false, DET, 66>);
+    else go(k_bpT_lds<KZ, false, DET, 0>);
+}
+
+template <bool DET>
+void launch_bpT_kz(const KParams &k, hipStream_t s, const float *gvol, void *gFout, const double *fscale) {
+    switch (k.bp_kz) {
+        case 8: launch_bpT<8, DET>(k, s, gvol, gFout, fscale); break;
+        case 32: launch_bpT<32, DET>(k, s, gvol, gFout, fscale); break;
+        default: launch_bpT<16, DET>(k, s, gvol, gFout, fscale); break;
+    }
 }
 
 // ----------------------------------------------------------------------------- fixed point
@@ -405,17 +452,7 @@ __global__ __launch_bounds__(kNT) void k_fixed_to_float(const unsigned long long
 }  // namespace
 
 hipError_t launch_backproject_T(const KParams &k, const float *gvol, float *gFbar, hipStream_t s) {
-    const dim3 grid((unsigned)k.bp_tiles_x, (unsigned)k.bp_tiles_y, (unsigned)(k.n_pitches * k.bp_runs));
-    const BpArgs a = bp_args(k);
-    const uint2 *boxes = reinterpret_cast<const uint2 *>(k.boxes);
-    const float4 *rays = reinterpret_cast<const float4 *>(k.tref);
-    const bool fb = !k.bp_all_fit;
-    const int ser = series_serves(k);
-    switch (k.bp_kz) {
-        case 8: launch_bpT<8, false>(fb, grid, s, a, gvol, gFbar, nullptr, k.rows, k.cols, k.first_view, k.view, boxes, rays, ser); break;
-        case 32: launch_bpT<32, false>(fb, grid, s, a, gvol, gFbar, nullptr, k.rows, k.cols, k.first_view, k.view, boxes, rays, ser); break;
-        default: launch_bpT<16, false>(fb, grid, s, a, gvol, gFbar, nullptr, k.rows, k.cols, k.first_view, k.view, boxes, rays, ser); break;
-    }
+    launch_bpT_kz<false>(k, s, gvol, gFbar, nullptr);
     return hipGetLastError();
 }
 
@@ -431,17 +468,7 @@ hipError_t launch_backproject_T_fixed(const KParams &k, const float *gvol, unsig
     hipLaunchKernelGGL(k_fixed_scale, dim3(1), dim3(kNT), 0, s, (const float *)part, np, bound, S);
     hipError_t e = launch_zero(gF64, ngf * 8, s);
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)k.bp_tiles_x, (unsigned)k.bp_tiles_y, (unsigned)(k.n_pitches * k.bp_runs));
-    const BpArgs a = bp_args(k);
-    const uint2 *boxes = reinterpret_cast<const uint2 *>(k.boxes);
-    const float4 *rays = reinterpret_cast<const float4 *>(k.tref);
-    const bool fb = !k.bp_all_fit;
-    const int ser = series_serves(k);
-    switch (k.bp_kz) {
-        case 8: launch_bpT<8, true>(fb, grid, s, a, gvol, gF64, S, k.rows, k.cols, k.first_view, k.view, boxes, rays, ser); break;
-        case 32: launch_bpT<32, true>(fb, grid, s, a, gvol, gF64, S, k.rows, k.cols, k.first_view, k.view, boxes, rays, ser); break;
-        default: launch_bpT<16, true>(fb, grid, s, a, gvol, gF64, S, k.rows, k.cols, k.first_view, k.view, boxes, rays, ser); break;
-    }
+    launch_bpT_kz<true>(k, s, gvol, gF64, S);
     return hipGetLastError();
 }
 

@@ -1,0 +1,48 @@
+"""Backprojector and adjoint over the footprint-box shapes their kernels are built for: boxes of
+at most 32 and 64 columns, wider ones, deeper than 32 rows, and beyond the LDS (HBM path), on
+ragged grids, against the FP64 oracle."""
+import numpy as np
+import pytest
+
+import oracle as O
+from synth import configs, phantom
+
+torch = pytest.importorskip("torch")
+K = pytest.importorskip("paper_2201_02309_amd")
+
+pytestmark = pytest.mark.gpu
+
+# nxy, columns, rows, slices per pitch -> box rows x columns
+SHAPES = [(40, 24, 24, 24, 28, 17), (20, 47, 8, 12, 12, 46), (20, 100, 12, 12, 16, 90),
+          (20, 180, 20, 12, 24, 158), (18, 420, 40, 12, 44, 405)]
+
+
+@pytest.mark.parametrize("bp_slices", [16, 8, 32])
+@pytest.mark.parametrize("nxy,cols,rows,spp,box_rows,box_cols", SHAPES)
+def test_box_shapes(nxy, cols, rows, spp, box_rows, box_cols, bp_slices):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = configs.tiny(nxy=nxy, nz=14, cols=cols, rows=rows, views_per_turn=72, turns=3, feed=24.0,
+                      dxy=2.0, slices_per_pitch=spp)
+    geom, gr = wl.geom.as_dict(), wl.grid.as_dict()
+    print(f"[case] {nxy}^2, detector {rows} x {cols}, runs of {bp_slices}", flush=True)
+    plan = K.Plan(geom, gr, device=0, bp_slices=bp_slices)
+    det = K.Plan(geom, gr, device=0, bp_slices=bp_slices, deterministic_adjoint=True)
+    if bp_slices == 16:
+        assert (plan.info["bp_box_rows"], plan.info["bp_box_cols"]) == (box_rows, box_cols)
+    sino = phantom.project(phantom.make_phantom(wl.phantom, gr, wl.seed), geom).astype(np.float32)
+    ref, valid = O.recon(O.Scan(geom), gr, sino)
+    vol = K.recon(plan, torch.from_numpy(sino).cuda()).cpu().numpy()
+    err = np.linalg.norm((vol - ref)[valid]) / np.linalg.norm(ref[valid])
+    y = np.random.default_rng(nxy).normal(size=ref.shape).astype(np.float32)
+    tref = O.recon_T(O.Scan(geom), gr, y.astype(np.float64))
+    yd = torch.from_numpy(y).cuda()
+    errs = []
+    for p in (plan, det):
+        g = K.recon_backward(p, yd).double().cpu().numpy()
+        errs.append(np.linalg.norm(g - tref) / np.linalg.norm(tref))
+    print(f"[parity] recon {err:.2e}, adjoint {errs[0]:.2e}, deterministic {errs[1]:.2e}", flush=True)
+    # the parity bar; a random cotangent sees the column coordinate's float32 rounding itself,
+    # up to an ulp of the box's width in cells
+    assert np.all(vol[~valid] == 0) and err <= 1e-5
+    assert max(errs) <= 1e-5 + 2.0 ** -23 * box_cols
