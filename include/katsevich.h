@@ -322,6 +322,38 @@ int katsevich_rmse_ssim(const float *d_f, const float *d_ref, uint64_t n, double
 int katsevich_rmse_ssim_noscratch(const float *d_f, const float *d_ref, uint64_t n, double *d_result,
                                   void *stream);
 
+/* ---- 3 x 3 x 3 convolutions of the dual-domain network (Sec. III-A) on the float32 matrix cores.
+ * Plan-free, asynchronous on stream, no device allocation.  shape: batch, input channels, output
+ * channels (at most 16 each), depth, height, width (host array of 6); strides: of batch, channel and
+ * depth in floats (host arrays of 3; rows contiguous, planes of height x width).  Errors:
+ * KATS_EINVAL, KATS_EWORKSPACE, KATS_EHIP. */
+
+/* y = bias + zero-padded (1 voxel) correlation of x with the weights w [out][in][3][3][3]; bias
+ * may be null.  transposed: w is [in][out][3][3][3] read flipped, which is the gradient of that
+ * convolution with respect to its input (x: the gradient of its output). */
+int katsevich_conv3(const float *d_x, const int64_t *x_strides, const float *d_w, const float *d_bias,
+                    float *d_y, const int64_t *y_strides, const int64_t *shape, int transposed,
+                    void *stream);
+
+/* Gradients with respect to the weights and the bias from the input x and the gradient dy of the
+ * output: d_dw [out][in][3][3][3], d_db [out], either null if not wanted.  d_scratch:
+ * katsevich_conv3_scratch_bytes() bytes (a fixed size).  Bit-reproducible. */
+uint64_t katsevich_conv3_scratch_bytes(void);
+int katsevich_conv3_grad(const float *d_x, const int64_t *x_strides, const float *d_dy,
+                         const int64_t *y_strides, const int64_t *shape, float *d_dw, float *d_db,
+                         void *d_scratch, uint64_t scratch_bytes, void *stream);
+
+/* Gradients of PReLU (x > 0 ? x : slope[c] x) on [batch][channel][depth] planes of height x width
+ * dense samples (shape: batch, channels, depth, height, width; strides as above): d_dx and d_dslope
+ * [channels] from the input x and the gradient dy of the output.  d_scratch:
+ * katsevich_prelu_scratch_bytes(shape) bytes (0: the shape is not accepted), 8-byte aligned.
+ * Bit-reproducible. */
+uint64_t katsevich_prelu_scratch_bytes(const int64_t *shape);
+int katsevich_prelu_grad(const float *d_x, const int64_t *x_strides, const float *d_dy,
+                         const int64_t *dy_strides, const float *d_slope, float *d_dx,
+                         const int64_t *dx_strides, float *d_dslope, const int64_t *shape,
+                         void *d_scratch, uint64_t scratch_bytes, void *stream);
+
 /* Free a plan (NULL is ignored).  Device buffers stay with the caller. */
 void katsevich_plan_destroy(katsevich_plan_t plan);
 

@@ -24,7 +24,7 @@ DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-p
           "-munsafe-fp-atomics"]
 SOURCES = [("plan.cpp", False), ("capi.cpp", False), ("filter.hip", True), ("bp.hip", True),
            ("bp_adjoint.hip", True), ("plan_gpu.hip", True), ("data.hip", True),
-           ("hilbert_mfma.hip", True)]
+           ("hilbert_mfma.hip", True), ("conv3.hip", True)]
 
 
 def _run(cmd):

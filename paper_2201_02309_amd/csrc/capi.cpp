@@ -562,6 +562,127 @@ int katsevich_rmse_ssim_noscratch(const float *d_f, const float *d_ref, uint64_t
     return KATS_OK;
 }
 
+// Shape and stride checks of the convolutions; fills the arguments they share.
+static int conv3_args(const char *who, const float *x, const int64_t *xs, const float *y, const int64_t *ys,
+                      const int64_t *shape, kats::Conv3Args &a) {
+    if (!x || !xs || !y || !ys || !shape) return fail(KATS_EINVAL, std::string(who) + ": null argument");
+    for (int i = 0; i < 6; ++i)
+        if (shape[i] < 1 || shape[i] > INT32_MAX)
+            return fail(KATS_EINVAL, std::string(who) + ": a size is not in 1 .. 2^31 - 1");
+    if (shape[1] > 16 || shape[2] > 16)
+        return fail(KATS_EINVAL, std::string(who) + ": more than 16 channels");
+    // grid limits of the launches (65535 in y and z, tiles in x)
+    if (shape[0] > 65535 || shape[3] > 4 * 65535 || ((shape[4] + 7) / 8) * ((shape[5] + 31) / 32) > INT32_MAX / shape[0])
+        return fail(KATS_EINVAL, std::string(who) + ": volume too large");
+    // a lane's offset within a depth is 32 bits
+    const int64_t plane = shape[4] * shape[5];
+    for (const int64_t c : {xs[1], ys[1]})
+        if (c < 0 || 16 * c + plane > (int64_t)1 << 30)
+            return fail(KATS_EINVAL, std::string(who) + ": channel stride negative or too large");
+    a.x = x;
+    a.B = (int)shape[0];
+    a.cin = (int)shape[1];
+    a.cout = (int)shape[2];
+    a.D = (int)shape[3];
+    a.H = (int)shape[4];
+    a.W = (int)shape[5];
+    a.xb = xs[0];
+    a.xc = xs[1];
+    a.xd = xs[2];
+    a.yb = ys[0];
+    a.yc = ys[1];
+    a.yd = ys[2];
+    return KATS_OK;
+}
+
+int katsevich_conv3(const float *d_x, const int64_t *x_strides, const float *d_w, const float *d_bias, float *d_y,
+                    const int64_t *y_strides, const int64_t *shape, int transposed, void *stream) {
+    g_err.clear();
+    kats::Conv3Args a{};
+    const int st = conv3_args("katsevich_conv3", d_x, x_strides, d_y, y_strides, shape, a);
+    if (st) return st;
+    if (!d_w) return fail(KATS_EINVAL, "katsevich_conv3: null weights");
+    a.w = d_w;
+    a.bias = d_bias;
+    a.y = d_y;
+    a.flip = transposed ? 1 : 0;
+    a.wm = transposed ? 27 : 27 * a.cin;
+    a.wk = transposed ? 27 * a.cout : 27;
+    const hipError_t e = kats::launch_conv3(a, static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "katsevich_conv3: launch");
+    return KATS_OK;
+}
+
+uint64_t katsevich_conv3_scratch_bytes(void) { return (uint64_t)kats::kConv3Blocks * kats::kConv3Part * 4; }
+
+int katsevich_conv3_grad(const float *d_x, const int64_t *x_strides, const float *d_dy, const int64_t *y_strides,
+                         const int64_t *shape, float *d_dw, float *d_db, void *d_scratch, uint64_t scratch_bytes,
+                         void *stream) {
+    g_err.clear();
+    kats::Conv3Args a{};
+    const int st = conv3_args("katsevich_conv3_grad", d_x, x_strides, d_dy, y_strides, shape, a);
+    if (st) return st;
+    if (!d_scratch || scratch_bytes < katsevich_conv3_scratch_bytes())
+        return fail(KATS_EWORKSPACE, "katsevich_conv3_grad: scratch too small");
+    const hipError_t e = kats::launch_conv3_wgrad(a, d_dy, d_dw, d_db, static_cast<float *>(d_scratch),
+                                                  static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "katsevich_conv3_grad: launch");
+    return KATS_OK;
+}
+
+static int prelu_shape(const int64_t *shape, uint64_t &blocks) {
+    if (!shape) return fail(KATS_EINVAL, "katsevich_prelu_grad: null argument");
+    uint64_t planes = 1;
+    for (int i = 0; i < 5; ++i) {
+        if (shape[i] < 1 || shape[i] > INT32_MAX)
+            return fail(KATS_EINVAL, "katsevich_prelu_grad: a size is not in 1 .. 2^31 - 1");
+        if (i < 3) planes *= (uint64_t)shape[i];
+        if (planes > INT32_MAX) return fail(KATS_EINVAL, "katsevich_prelu_grad: volume too large");
+    }
+    const uint64_t n = (uint64_t)shape[3] * (uint64_t)shape[4];
+    const uint64_t chunks = (n + (uint64_t)kats::kPreluBlock - 1) / (uint64_t)kats::kPreluBlock;
+    if (chunks > INT32_MAX / planes) return fail(KATS_EINVAL, "katsevich_prelu_grad: volume too large");
+    blocks = planes * chunks;
+    return KATS_OK;
+}
+
+uint64_t katsevich_prelu_scratch_bytes(const int64_t *shape) {
+    g_err.clear();
+    uint64_t blocks = 0;
+    return prelu_shape(shape, blocks) == KATS_OK ? blocks * 8 : 0;
+}
+
+int katsevich_prelu_grad(const float *d_x, const int64_t *x_strides, const float *d_dy, const int64_t *dy_strides,
+                         const float *d_slope, float *d_dx, const int64_t *dx_strides, float *d_dslope,
+                         const int64_t *shape, void *d_scratch, uint64_t scratch_bytes, void *stream) {
+    g_err.clear();
+    if (!d_x || !x_strides || !d_dy || !dy_strides || !d_slope || !d_dx || !dx_strides || !d_dslope)
+        return fail(KATS_EINVAL, "katsevich_prelu_grad: null argument");
+    uint64_t blocks = 0;
+    const int st = prelu_shape(shape, blocks);
+    if (st) return st;
+    if (!d_scratch || scratch_bytes < blocks * 8 || ((uintptr_t)d_scratch & 7))
+        return fail(KATS_EWORKSPACE, "katsevich_prelu_grad: scratch too small or not 8-byte aligned");
+    kats::PreluArgs a{};
+    a.x = d_x;
+    a.dy = d_dy;
+    a.slope = d_slope;
+    a.dx = d_dx;
+    for (int i = 0; i < 3; ++i) {
+        a.xs[i] = x_strides[i];
+        a.gs[i] = dy_strides[i];
+        a.os[i] = dx_strides[i];
+    }
+    a.B = (int)shape[0];
+    a.C = (int)shape[1];
+    a.D = (int)shape[2];
+    a.n = (long long)shape[3] * shape[4];
+    const hipError_t e = kats::launch_prelu_grad(a, d_dslope, static_cast<double *>(d_scratch),
+                                                 static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "katsevich_prelu_grad: launch");
+    return KATS_OK;
+}
+
 int katsevich_backproject_batch(const katsevich_plan_t *plans, const float *const *d_gF,
                                 float *const *d_vol, int n, void *stream) {
     g_err.clear();

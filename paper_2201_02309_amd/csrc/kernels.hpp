@@ -116,6 +116,34 @@ hipError_t launch_filter_T_views(const KParams &k, const float *gFbar, float *g4
 hipError_t launch_deriv_T(const KParams &k, const float *g2bar, float *gsino, long long n0,
                           long long count, hipStream_t s);
 
+// ---- 3 x 3 x 3 convolutions of the network (conv3.hip).  Strides in floats: batch, channel and
+// depth of x and y (rows of W, planes of H rows); weight of (output m, input k, tap t) at
+// m wm + k wk + (flip ? 26 - t : t).
+struct Conv3Args {
+    const float *x, *w, *bias;
+    float *y;
+    long long xb, xc, xd, yb, yc, yd;
+    int B, cin, cout, D, H, W, wm, wk, flip;
+    int tiles_w, tiles_h, dseg, nseg;       // set by the launchers
+};
+constexpr int kConv3Part = 27 * 256 + 16;   // floats of one workgroup's weight-gradient partial
+constexpr int kConv3Blocks = 512;           // its persistent workgroups (two per CU)
+hipError_t launch_conv3(Conv3Args a, hipStream_t s);
+// a: x and the strides of dy in yb, yc, yd; dw [cout][cin][27] and db [cout] (either may be null);
+// part: kConv3Blocks * kConv3Part floats
+hipError_t launch_conv3_wgrad(Conv3Args a, const float *dy, float *dw, float *db, float *part, hipStream_t s);
+
+// PReLU gradient on [batch][channel][depth] planes of n dense samples (strides of the three in floats)
+struct PreluArgs {
+    const float *x, *dy, *slope;
+    float *dx;
+    long long xs[3], gs[3], os[3];
+    int B, C, D, chunks;                    // chunks: set by the launcher
+    long long n;
+};
+constexpr long long kPreluBlock = 8192;     // samples per block; one float64 partial each
+hipError_t launch_prelu_grad(PreluArgs a, float *dslope, double *part, hipStream_t s);
+
 // ---- Device plan builder (plan_gpu.hip): float64 scalars of the plan, exactly as the host
 // builder holds them.
 struct DevPlanArgs {

@@ -80,7 +80,9 @@ EXPORTED = ["katsevich_plan", "katsevich_plan_query", "katsevich_plan_bind",
             "katsevich_plan_destroy", "katsevich_status_string", "katsevich_last_error",
             "katsevich_plan_device", "katsevich_plan_device_sizes",
             "katsevich_sparse_upsample", "katsevich_data_scratch_bytes", "katsevich_max",
-            "katsevich_add_noise", "katsevich_rmse_ssim", "katsevich_rmse_ssim_noscratch"]
+            "katsevich_add_noise", "katsevich_rmse_ssim", "katsevich_rmse_ssim_noscratch",
+            "katsevich_conv3", "katsevich_conv3_grad", "katsevich_conv3_scratch_bytes",
+            "katsevich_prelu_grad", "katsevich_prelu_scratch_bytes"]
 
 _lib = None
 
@@ -127,6 +129,21 @@ def load_library(path: str = LIB_PATH):
     lib.katsevich_rmse_ssim.restype = c_int
     lib.katsevich_rmse_ssim_noscratch.argtypes = [c_void_p, c_void_p, c_uint64, c_void_p, c_void_p]
     lib.katsevich_rmse_ssim_noscratch.restype = c_int
+    lib.katsevich_conv3.argtypes = [c_void_p, POINTER(c_int64), c_void_p, c_void_p, c_void_p,
+                                    POINTER(c_int64), POINTER(c_int64), c_int, c_void_p]
+    lib.katsevich_conv3.restype = c_int
+    lib.katsevich_conv3_scratch_bytes.argtypes = []
+    lib.katsevich_conv3_scratch_bytes.restype = c_uint64
+    lib.katsevich_conv3_grad.argtypes = [c_void_p, POINTER(c_int64), c_void_p, POINTER(c_int64),
+                                         POINTER(c_int64), c_void_p, c_void_p, c_void_p, c_uint64,
+                                         c_void_p]
+    lib.katsevich_conv3_grad.restype = c_int
+    lib.katsevich_prelu_scratch_bytes.argtypes = [POINTER(c_int64)]
+    lib.katsevich_prelu_scratch_bytes.restype = c_uint64
+    lib.katsevich_prelu_grad.argtypes = [c_void_p, POINTER(c_int64), c_void_p, POINTER(c_int64), c_void_p,
+                                         c_void_p, POINTER(c_int64), c_void_p, POINTER(c_int64), c_void_p,
+                                         c_uint64, c_void_p]
+    lib.katsevich_prelu_grad.restype = c_int
     lib.katsevich_plan_destroy.argtypes = [c_void_p]
     lib.katsevich_plan_destroy.restype = None
     lib.katsevich_status_string.argtypes = [c_int]
@@ -496,6 +513,70 @@ def rmse_ssim_noscratch(f, ref, result=None):
                                                   c_uint64(f.numel()), c_void_p(result.data_ptr()),
                                                   _stream_handle(f.device)))
     return result
+
+
+# ---------------------------------------------------------------- network convolutions
+def _volume_strides(t):
+    """Batch, channel and depth strides of [B, C, D, H, W] for the convolution calls."""
+    return (c_int64 * 3)(*t.stride()[:3])
+
+
+def rows_dense(t):
+    """Whether every [H, W] plane of t is stored densely, as the convolution calls need."""
+    H, W = t.shape[-2:]
+    return (W == 1 or t.stride(-1) == 1) and (H == 1 or t.stride(-2) == W)
+
+
+def conv3(x, w, bias=None, transposed=False):
+    """katsevich_conv3: 3x3x3 convolution (zero padding 1) of x [B, cin, D, H, W] with w [cout, cin,
+    3, 3, 3], or with `transposed` its gradient with respect to the input, w [cin, cout, 3, 3, 3].
+    The result is stored as [B, D, cout, H, W].  x: float32, planes dense."""
+    import torch
+    B, cin, D, H, W = x.shape
+    cout = w.shape[1 if transposed else 0]
+    y = torch.empty((B, D, cout, H, W), dtype=torch.float32, device=x.device).permute(0, 2, 1, 3, 4)
+    lib = load_library()
+    with torch.cuda.device(x.device):
+        _check(lib, lib.katsevich_conv3(
+            c_void_p(x.data_ptr()), _volume_strides(x), c_void_p(w.data_ptr()),
+            c_void_p(0 if bias is None else bias.data_ptr()), c_void_p(y.data_ptr()), _volume_strides(y),
+            (c_int64 * 6)(B, cin, cout, D, H, W), int(transposed), _stream_handle(x.device)))
+    return y
+
+
+def conv3_grad(x, dy, weight_shape):
+    """katsevich_conv3_grad: gradients (dw, db) of a 3x3x3 convolution from its input and the
+    gradient of its output."""
+    import torch
+    B, cin, D, H, W = x.shape
+    lib = load_library()
+    with torch.cuda.device(x.device):
+        dw = torch.empty(weight_shape, dtype=torch.float32, device=x.device)
+        db = torch.empty(weight_shape[0], dtype=torch.float32, device=x.device)
+        part = torch.empty(int(lib.katsevich_conv3_scratch_bytes()), dtype=torch.uint8, device=x.device)
+        _check(lib, lib.katsevich_conv3_grad(
+            c_void_p(x.data_ptr()), _volume_strides(x), c_void_p(dy.data_ptr()), _volume_strides(dy),
+            (c_int64 * 6)(B, cin, weight_shape[0], D, H, W), c_void_p(dw.data_ptr()), c_void_p(db.data_ptr()),
+            c_void_p(part.data_ptr()), c_uint64(part.numel()), _stream_handle(x.device)))
+    return dw, db
+
+
+def prelu_grad(x, dy, slope):
+    """katsevich_prelu_grad: (dx, dslope) of a PReLU with one slope per channel; dx is stored as
+    [B, D, C, H, W]."""
+    import torch
+    B, C, D, H, W = x.shape
+    lib = load_library()
+    with torch.cuda.device(x.device):
+        dx = torch.empty((B, D, C, H, W), dtype=torch.float32, device=x.device).permute(0, 2, 1, 3, 4)
+        dslope = torch.empty(C, dtype=torch.float32, device=x.device)
+        shape = (c_int64 * 5)(B, C, D, H, W)
+        part = torch.empty(max(int(lib.katsevich_prelu_scratch_bytes(shape)), 8), dtype=torch.uint8, device=x.device)
+        _check(lib, lib.katsevich_prelu_grad(
+            c_void_p(x.data_ptr()), _volume_strides(x), c_void_p(dy.data_ptr()), _volume_strides(dy),
+            c_void_p(slope.data_ptr()), c_void_p(dx.data_ptr()), _volume_strides(dx), c_void_p(dslope.data_ptr()),
+            shape, c_void_p(part.data_ptr()), c_uint64(part.numel()), _stream_handle(x.device)))
+    return dx, dslope
 
 
 def recon_backward(plan: Plan, grad_vol, out=None, ws=None):

@@ -5,10 +5,11 @@ with Adam.
 The domain-transfer layer is the library's differentiable reconstruction (KatsevichFn:
 katsevich_recon forward, its exact adjoint katsevich_recon_backward backward) on a plan of
 one pitch: the sinogram window that reconstructs that pitch's slices goes in, the slices
-come out.  The two subnetworks are PyTorch convolutions (MIOpen on ROCm); each 3x3x3
-convolution runs as one 2-D convolution over the three depth-shifted copies of its input
-stacked as channels, with depth folded into the batch: MIOpen's 3-D convolution backward
-measured ~150x slower than this form on the network's shapes.
+come out.  The gradients of the subnetworks' 3x3x3 convolutions and PReLUs, and the convolutions
+of inference, run on the library's kernels (katsevich_conv3, katsevich_conv3_grad,
+katsevich_prelu_grad: float32 matrix cores); a training step's forward, other types, devices,
+channel counts and tracing or transforming callers take one PyTorch 2-D convolution over the three
+depth-shifted copies of the input stacked as channels, with depth folded into the batch.
 """
 from __future__ import annotations
 
@@ -18,13 +19,95 @@ import torch
 import torch.nn.functional as F
 from torch import nn
 
+from . import katsevich as _K
 from .katsevich import KatsevichFn, Plan
+
+
+def _conv3x3x3(x, weight, bias):
+    """The convolution as a 2-D convolution: output depth d sees input depths d-1, d, d+1 stacked
+    as 3 cin channels.  Any type and device, every order of derivative."""
+    B, C, D, H, W = x.shape
+    xp = F.pad(x, (0, 0, 0, 0, 1, 1))
+    stack = torch.cat([xp[:, :, k:k + D] for k in range(3)], dim=1)      # [B, 3C, D, H, W]
+    stack = stack.permute(0, 2, 1, 3, 4).reshape(B * D, 3 * C, H, W)
+    cout = weight.shape[0]
+    w2 = weight.permute(0, 2, 1, 3, 4).reshape(cout, 3 * C, 3, 3)
+    y = F.conv2d(stack, w2, bias, padding=1)
+    return y.reshape(B, D, cout, H, W).permute(0, 2, 1, 3, 4)
+
+
+def _plain(*tensors):
+    """Whether every tensor is a plain float32 one of the same GPU, and no autocast, tracing,
+    compilation, forward-mode derivative, function transform or dispatch mode is at work, which
+    need torch's operators."""
+    for t in tensors:
+        if type(t) not in (torch.Tensor, nn.Parameter) or t.dtype != torch.float32 or not t.is_cuda \
+                or t.device != tensors[0].device or not torch._C._has_storage(t):
+            return False
+    return not (torch.is_autocast_enabled("cuda") or torch.jit.is_tracing() or torch.jit.is_scripting()
+                or torch.compiler.is_compiling() or torch.autograd.forward_ad._current_level >= 0
+                or torch._C._functorch.peek_interpreter_stack() is not None
+                or torch._C._len_torch_dispatch_stack() > 0)
+
+
+def _native_volume(x, channels):
+    """Whether x is a [B, channels, D, H, W] volume within the kernels' grids and 32-bit offsets."""
+    if x.dim() != 5 or x.numel() == 0 or x.shape[1] != channels:
+        return False
+    B, C, D, H, W = x.shape
+    return (B <= 65535 and D <= 4 * 65535 and (16 * D + 1) * H * W <= 1 << 30
+            and B * D * C < 1 << 31 and B * ((H + 7) // 8) * ((W + 31) // 32) < 1 << 31)
+
+
+def _native_conv(x, weight, bias):
+    """Whether the library's kernels take this convolution (at most 16 channels on either side)."""
+    if x.dim() != 5 or not _plain(x, weight, bias):
+        return False
+    cin, cout = x.shape[1], weight.shape[0]
+    return (1 <= cout <= 16 and cin <= 16 and tuple(weight.shape) == (cout, cin, 3, 3, 3)
+            and tuple(bias.shape) == (cout,) and _native_volume(x, cin))
+
+
+class _Conv3Fn(torch.autograd.Function):
+    """_conv3x3x3 with its gradients on the library's kernels; a derivative that is itself to be
+    differentiated, or whose gradient the kernels do not take, goes through _conv3x3x3 again.  x and
+    weight are kept as they are: the caller hands over tensors that nothing changes before the
+    backward.  The forward of a training step stays torch's: PReLU's derivative jumps at 0, so
+    another rounding of the activations would move a whole network's gradients by 1e-3."""
+
+    @staticmethod
+    def forward(ctx, x, weight, bias):
+        ctx.save_for_backward(x, weight)
+        return _conv3x3x3(x, weight, bias)
+
+    @staticmethod
+    def backward(ctx, gy):
+        x, weight = ctx.saved_tensors
+        want = ctx.needs_input_grad
+        again = torch.is_grad_enabled()
+        if again or not _native_conv(gy, weight.transpose(0, 1), x.new_empty(x.shape[1])):
+            with torch.enable_grad():
+                bias = weight.new_zeros(weight.shape[0], requires_grad=True)   # its value plays no part
+                args = [t if t.requires_grad else t.detach().requires_grad_(n)
+                        for t, n in zip((x, weight, bias), want)]
+                grads = iter(torch.autograd.grad(_conv3x3x3(*args), [t for t, n in zip(args, want) if n],
+                                                 gy, create_graph=again))
+            return tuple(next(grads) if n else None for n in want)
+        gy = gy if _K.rows_dense(gy) else gy.contiguous()
+        gx = _K.conv3(gy, weight.contiguous(), transposed=True) if want[0] else None
+        gw = gb = None
+        if want[1] or want[2]:
+            gw, gb = _K.conv3_grad(x if _K.rows_dense(x) else x.contiguous(), gy, tuple(weight.shape))
+        return gx, gw if want[1] else None, gb if want[2] else None
 
 
 class Conv3x3x3(nn.Module):
     """3-D convolution with a 3x3x3 kernel and zero padding 1 (as nn.Conv3d(cin, cout, 3,
-    padding=1)), computed as a 2-D convolution: output depth d sees input depths d-1, d,
-    d+1 stacked as 3 cin channels."""
+    padding=1)).  Its input and parameters may be changed in place before the backward: it keeps
+    copies of them (of the input only while `copy_input` holds; a network whose forward leaves a
+    convolution's input alone clears it there)."""
+
+    copy_input = True
 
     def __init__(self, cin: int, cout: int):
         super().__init__()
@@ -33,14 +116,48 @@ class Conv3x3x3(nn.Module):
         self.bias = nn.Parameter(ref.bias.detach().clone())
 
     def forward(self, x):                                   # x [B, C, D, H, W]
-        B, C, D, H, W = x.shape
-        xp = F.pad(x, (0, 0, 0, 0, 1, 1))
-        stack = torch.cat([xp[:, :, k:k + D] for k in range(3)], dim=1)      # [B, 3C, D, H, W]
-        stack = stack.permute(0, 2, 1, 3, 4).reshape(B * D, 3 * C, H, W)
-        cout = self.weight.shape[0]
-        w2 = self.weight.permute(0, 2, 1, 3, 4).reshape(cout, 3 * C, 3, 3)
-        y = F.conv2d(stack, w2, self.bias, padding=1)
-        return y.reshape(B, D, cout, H, W).permute(0, 2, 1, 3, 4)
+        w, b = self.weight, self.bias
+        if not _native_conv(x, w, b):
+            return _conv3x3x3(x, w, b)
+        if torch.is_grad_enabled() and (x.requires_grad or w.requires_grad or b.requires_grad):
+            return _Conv3Fn.apply(x.clone() if self.copy_input and w.requires_grad else x, w.clone(), b)
+        return _K.conv3(x if _K.rows_dense(x) else x.contiguous(), w.contiguous(), b.contiguous())
+
+
+class _PReLUFn(torch.autograd.Function):
+    """PReLU with one slope per channel, its gradients on the library's kernel; a derivative that is
+    itself to be differentiated, or whose gradient the kernel does not take, goes through torch."""
+
+    @staticmethod
+    def forward(ctx, x, weight):
+        ctx.save_for_backward(x, weight)
+        return F.prelu(x, weight)
+
+    @staticmethod
+    def backward(ctx, gy):
+        x, weight = ctx.saved_tensors
+        want = ctx.needs_input_grad
+        again = torch.is_grad_enabled()
+        if again or not _plain(gy, x, weight):
+            with torch.enable_grad():
+                args = [t if t.requires_grad else t.detach().requires_grad_(n) for t, n in zip((x, weight), want)]
+                grads = iter(torch.autograd.grad(F.prelu(*args), [t for t, n in zip(args, want) if n], gy,
+                                                 create_graph=again))
+            return tuple(next(grads) if n else None for n in want)
+        gx, gw = _K.prelu_grad(x if _K.rows_dense(x) else x.contiguous(),
+                               gy if _K.rows_dense(gy) else gy.contiguous(), weight.contiguous())
+        return gx if want[0] else None, gw if want[1] else None
+
+
+class PReLU(nn.PReLU):
+    """nn.PReLU whose gradients on float32 volumes of one GPU run on the library's kernel."""
+
+    def forward(self, x):
+        w = self.weight
+        if torch.is_grad_enabled() and (x.requires_grad or w.requires_grad) and _plain(x, w) \
+                and _native_volume(x, w.numel()):
+            return _PReLUFn.apply(x, w)
+        return super().forward(x)
 
 
 class SubNet(nn.Module):
@@ -53,8 +170,10 @@ class SubNet(nn.Module):
         super().__init__()
         self.convs = nn.ModuleList([Conv3x3x3(1 if i == 0 else channels, channels)
                                     for i in range(blocks)])
-        self.acts = nn.ModuleList([nn.PReLU(channels) for _ in range(blocks)])
+        self.acts = nn.ModuleList([PReLU(channels) for _ in range(blocks)])
         self.out = Conv3x3x3(channels, 1)
+        for conv in (*self.convs[1:], self.out):
+            conv.copy_input = False        # forward() makes these inputs and does not change them
 
     def forward(self, x):                          # x [B, 1, D, H, W]
         h = x
