@@ -43,11 +43,6 @@ __device__ inline T ldg(const T *ptr) {
 
 constexpr int kT = kBpTile;       // 16
 constexpr int kNT = kT * kT;      // 256 lanes
-constexpr int kLP = kBpBoxCols;   // LDS tile row pitch (floats) = max box columns
-// LDS tile depth (max box rows) of a slice run: runs of 32 slices span up to ~60 detector
-// rows, shorter runs fit 32.
-template <int KZ>
-constexpr int lds_rows() { return KZ >= 32 ? 2 * kBpBoxRows : kBpBoxRows; }
 constexpr int kKG = 4;            // slices per branch group
 
 // The scalars the backprojector needs (a slim kernel argument keeps SGPR pressure low).

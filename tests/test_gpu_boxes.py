@@ -1,6 +1,7 @@
 """Backprojector and adjoint over the footprint-box shapes their kernels are built for: boxes of
 at most 32 and 64 columns, wider ones, deeper than 32 rows, and beyond the LDS (HBM path), on
-ragged grids, against the FP64 oracle."""
+ragged grids, against the FP64 oracle; and the backprojector's splits of small grids over more
+workgroups."""
 import numpy as np
 import pytest
 
@@ -14,6 +15,7 @@ pytestmark = pytest.mark.gpu
 
 # nxy, columns, rows, slices per pitch -> box rows x columns
 SHAPES = [(40, 24, 24, 24, 28, 17), (20, 47, 8, 12, 12, 46), (20, 100, 12, 12, 16, 90),
+          (40, 24, 48, 10, 52, 17), (24, 60, 40, 8, 44, 48), (20, 130, 16, 12, 20, 116),
           (20, 180, 20, 12, 24, 158), (18, 420, 40, 12, 44, 405)]
 
 
@@ -46,3 +48,30 @@ def test_box_shapes(nxy, cols, rows, spp, box_rows, box_cols, bp_slices):
     # up to an ulp of the box's width in cells
     assert np.all(vol[~valid] == 0) and err <= 1e-5
     assert max(errs) <= 1e-5 + 2.0 ** -23 * box_cols
+
+
+# whole 16 x 16 x 16 tasks' worth of voxels: 64, 144, 294 and 478, on either side of each limit
+@pytest.mark.parametrize("nxy,nz", [(64, 64), (96, 64), (112, 96), (140, 100)])
+def test_splits(nxy, nz):
+    """16-slice runs, split over workgroups by the grid's size, against 8-slice runs, which never
+    are: sums of the same ~50 float32 terms in another order.  Alone, in stages and in a group the
+    bits are the same."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = configs.tiny(nxy=nxy, nz=nz, cols=96, rows=16, views_per_turn=72, turns=6, feed=48.0, dxy=2.0,
+                      slices_per_pitch=24)
+    geom, gr = wl.geom.as_dict(), wl.grid.as_dict()
+    print(f"[case] {nxy}^2 x {nz}", flush=True)
+    plan, ref_plan = K.Plan(geom, gr, device=0), K.Plan(geom, gr, device=0, bp_slices=8)
+    torch.manual_seed(0)
+    sino = torch.rand(geom["n_views"], geom["det_rows"], geom["det_cols"], device="cuda")
+    vol, ref = K.recon(plan, sino), K.recon(ref_plan, sino)
+    assert bool(((vol == 0) == (ref == 0)).all())
+    err = float((vol - ref).double().norm() / ref.double().norm())
+    print(f"[parity] {err:.2e}", flush=True)
+    assert err <= 25 * 2.0 ** -24
+    gF = K.filter_views(plan, sino)
+    assert torch.equal(K.backproject(plan, gF), vol)
+    other = K.filter_views(ref_plan, sino * 2)
+    both = K.backproject_batch([plan, plan], [gF, other])
+    assert torch.equal(both[0], vol) and torch.equal(both[1], K.backproject(plan, other))
