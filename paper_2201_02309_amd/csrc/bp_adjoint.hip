@@ -13,7 +13,7 @@ using namespace bpdev;
 
 // ---------------------------------------------------------------------------------
 // Adjoint of the backprojection, tiled like the forward kernel: the workgroup's 16 x 16
-// voxel columns x KZ slices, the same PI-window hull, group words and footprint boxes.  At
+// voxel columns x KZ slices, the same PI-window hull, group limits and footprint boxes.  At
 // each view every lane scatters its four bilinear weights times
 // dlambda/(2 pi) c_n / v* fbar(x) into the view's box held in LDS (LDS float64 atomics); the
 // box of the previous view is flushed meanwhile from the other buffer to g^F-bar with one
@@ -22,8 +22,7 @@ using namespace bpdev;
 // ---------------------------------------------------------------------------------
 // The adjoint's LDS boxes accumulate in float64: the hardware's LDS float64 atomic add is
 // several times faster here than its float32 one, and exact enough that the flushed float32
-// sums round once.  Group words are bytes while the groups fit in 4 bits, so that the
-// double-buffered boxes still leave room for four workgroups per CU.
+// sums round once.
 //
 // The boxes take the workgroup's dynamic LDS, sized by the plan's largest footprint box
 // (bpT_shape): rows of `pitch` accumulators, pitch = 2 (mod 32), so that a column's cells of
@@ -32,9 +31,7 @@ using namespace bpdev;
 // With the tile fixed at 32 rows x 64 columns, plans with larger boxes scattered those views'
 // taps to HBM atomics; the kernel's time for the 256 x 256 x 64 sparse-detector workload, whose
 // boxes are 49 x 25 cells, went from 50.4 to 7.5 ms, and with 40 x 79 boxes (256 x 256 x 32,
-// 736 columns, fixed point) from 12.1 to 5.6 ms.  Words cover hulls up to kHullT views (the largest hull of the 512^3 /
-// 55296-view workload is 1649).
-constexpr int kHullT = 1784;
+// 736 columns, fixed point) from 12.1 to 5.6 ms.
 constexpr unsigned kLdsBytes = 163840;    // per CU and workgroup on gfx950
 
 // One box buffer: rows x pitch accumulators.
@@ -46,11 +43,7 @@ struct BpTShape {
 // associative, so the result does not depend on the order of the atomics).
 template <int KZ, bool DET>
 struct BpTTypes {
-    static constexpr int NG = KZ / kKG;
-    using Word = typename std::conditional<(NG <= 4), unsigned char, unsigned short>::type;
     using Acc = typename std::conditional<DET, unsigned long long, double>::type;
-    static constexpr int kFull = NG <= 4 ? 4 : 8;
-    static constexpr unsigned kWordBytes = 4 * kHullT * sizeof(Word);
 };
 
 // v * S rounded to the nearest integer, two's complement (|v| S < 2^62 by the choice of S)
@@ -85,8 +78,8 @@ template <int KZ, bool FB, bool DET, int PITCH>
 __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *__restrict__ gFout,
                          const double *__restrict__ fscale, int rows, int cols, long long first_view,
                          const float4 *__restrict__ view_tab, const uint2 *__restrict__ box_tab,
-                         const float4 *__restrict__ ray_tab, int series, const BpTShape shape, int bxi,
-                         int byi, int bz, unsigned char *lds, int *red) {
+                         const float4 *__restrict__ ray_tab, int series, const BpTShape shape, int parts,
+                         int bxi, int byi, int bz, unsigned char *lds, int *red) {
     using Acc = typename BpTTypes<KZ, DET>::Acc;
     typedef __attribute__((address_space(3))) Acc LdsAcc;
     float *gFbar = static_cast<float *>(gFout);
@@ -94,19 +87,17 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
     const double fx = DET ? *fscale : 0.0;
     static_assert(KZ % kKG == 0 && KZ / kKG <= 8, "groups use 8-bit masks");
     constexpr int NG = KZ / kKG;
-    using Word = typename BpTTypes<KZ, DET>::Word;
-    constexpr int kFull = BpTTypes<KZ, DET>::kFull;
     const int pitch_a = PITCH ? PITCH : shape.pitch;
     const int cells = pitch_a * shape.rows;                  // of one buffer
     LdsAcc *box = (LdsAcc *)lds;
-    Word *words = reinterpret_cast<Word *>(lds + 2 * (size_t)cells * sizeof(Acc));
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int ix = bxi * kT + (tid & (kT - 1));
     const int iy = byi * kT + (tid >> 4);
-    const int pitch = bz / p.runs;
-    const int run = bz % p.runs;
+    const int part = bz % parts;
+    const int pitch = bz / parts / p.runs;
+    const int run = bz / parts % p.runs;
     const int j0 = run * KZ;
     const int slices = min(p.ns, p.nz - pitch * p.ns);
     const int nrun = min(KZ, slices - j0);
@@ -159,21 +150,22 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
     // both box buffers start zeroed (every flush leaves its cells zero again)
     for (int i = tid; i < 2 * cells; i += kNT) box[i] = 0;
     __syncthreads();
-    const int mlo = __builtin_amdgcn_readfirstlane(min(min(red[0], red[1]), min(red[2], red[3])));
-    const int mhi = __builtin_amdgcn_readfirstlane(max(max(red[4], red[5]), max(red[6], red[7])));
-    // (an empty hull, mlo = INT_MAX > mhi = INT_MIN, takes no words: mhi - mlo would overflow)
-    const bool use_words = mlo <= mhi && mhi - mlo < kHullT;
-    if (use_words) {
-        for (int w = lane; w <= mhi - mlo; w += 64) {
-            const int m = mlo + w;
-            unsigned word = 0;
+    int mlo = __builtin_amdgcn_readfirstlane(min(min(red[0], red[1]), min(red[2], red[3])));
+    int mhi = __builtin_amdgcn_readfirstlane(max(max(red[4], red[5]), max(red[6], red[7])));
+    if (parts > 1 && mlo <= mhi) {                           // this task's share of the hull
+        const int steps = (mhi - mlo) / parts + 1;
+        mlo += part * steps;
+        mhi = min(mhi, mlo + steps - 1);
+    }
+    // first view at which a group has started (lanes 0 ..), has ended, is past its voxels' first
+    // views, has a voxel near its last (as in the forward kernel)
+    int bound = INT_MAX;
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                if (m >= g_alo[g] && m <= g_ahi[g]) word |= 1u << g;
-                if (m >= g_flo[g] && m <= g_fhi[g]) word |= 1u << (kFull + g);
-            }
-            words[wave * kHullT + w] = (Word)word;
-        }
+    for (int g = 0; g < NG; ++g) {
+        bound = lane == g ? g_alo[g] : bound;
+        bound = lane == NG + g ? g_ahi[g] + 1 : bound;
+        bound = lane == 2 * NG + g ? g_flo[g] : bound;
+        bound = lane == 3 * NG + g ? min(g_fhi[g], INT_MAX - 1) + 1 : bound;
     }
     __syncthreads();
 
@@ -240,8 +232,8 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
         const float st = q * p.dz;
         const float rmax = (float)(b.nr - 2);
         const float mf = (float)m;
-        unsigned word = (1u << NG) - 1u;
-        if (use_words) word = __builtin_amdgcn_readfirstlane(words[wave * kHullT + m - mlo]);
+        const unsigned word = (unsigned)__ballot(m >= bound);
+        const unsigned active = word & ~(word >> NG), full = (word >> (2 * NG)) & ~(word >> (3 * NG));
         // the view's active slices in register order: each slice adds its row weights to
         // two pending rows (R, R+1) kept in registers; a row's two taps (columns c0, c0+1)
         // are scattered once the walk has moved past it, so slices that share detector
@@ -251,14 +243,14 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
             float P = 0.0f, Q = 0.0f;
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
-                if (!(word & (1u << g))) continue;
-                const bool full = word & (1u << (kFull + g));
+                if (!(active & (1u << g))) continue;
+                const bool inside = full & (1u << g);
 #pragma unroll
                 for (int s = 0; s < kKG; ++s) {
                     const int r = g * kKG + s;                // register
                     const float sl = (float)((r + off) & (KZ - 1));     // its slice
                     float a = vinv * fb[r];
-                    if (!full) a *= med3(fminf(mf - A[r], B[r] - mf), 0.0f, 1.0f);
+                    if (!inside) a *= med3(fminf(mf - A[r], B[r] - mf), 0.0f, 1.0f);
                     const float rr = med3(fmaf(sl, st, rb), 0.0f, rmax);
                     const int Rk = (int)rr;
                     const float a1 = a * __builtin_amdgcn_fractf(rr), a0 = a - a1;   // rows Rk, Rk+1
@@ -330,11 +322,11 @@ __global__ __launch_bounds__(kNT) void k_bpT_lds(BpArgs p, const float *__restri
                                                  const float4 *__restrict__ view_tab,
                                                  const uint2 *__restrict__ box_tab,
                                                  const float4 *__restrict__ ray_tab, int series,
-                                                 BpTShape shape) {
+                                                 BpTShape shape, int parts) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ int red[8];
     bpT_tile<KZ, FB, DET, PITCH>(p, fvol, gFout, fscale, rows, cols, first_view, view_tab, box_tab, ray_tab, series,
-                          shape, blockIdx.x, blockIdx.y, blockIdx.z, lds, red);
+                          shape, parts, blockIdx.x, blockIdx.y, blockIdx.z, lds, red);
 }
 
 // Whether the odd series serves every voxel's angle from its tile centre's ray: a voxel lies
@@ -364,7 +356,7 @@ template <int KZ, bool DET>
 BpTShape bpT_shape(const KParams &k, bool &fb, unsigned &bytes) {
     using T = BpTTypes<KZ, DET>;
     auto size = [](const BpTShape &s) {
-        return 2u * (unsigned)s.pitch * (unsigned)s.rows * (unsigned)sizeof(typename T::Acc) + T::kWordBytes;
+        return 2u * (unsigned)s.pitch * (unsigned)s.rows * (unsigned)sizeof(typename T::Acc);
     };
     BpTShape s{};
     s.pitch = ((k.bp_box_cols < 1 ? 1 : k.bp_box_cols) + 31) / 32 * 32 + 2;
@@ -378,9 +370,26 @@ BpTShape bpT_shape(const KParams &k, bool &fb, unsigned &bytes) {
     return s;
 }
 
+// Tasks that the views of a (tile, run) hull are split over.  A workgroup walks its hull view by
+// view at 3-4 us a view, so few tasks leave CUs idle behind that chain, and a last round of long
+// tasks does on larger grids; the boxes' sums meet in g^F-bar anyway.  Whole adjoint by reconstructed
+// voxels in units of 16 x 16 x 16 tasks, parts 1 / 4 / 8 / 16 / 32, us:
+//      4 (54^2 x 7)             1716 /  571 /  358 /  242 /  187
+//     59 (64^3)                 1376 /  458 /  357 /  312 /  281
+//    104 (169^2 x 15)           4224 / 1375 / 1290 / 1160 / 1102
+//    304 (512^2 x 10, network)  2864 / 2302 / 2228 / 2238 / 2364
+//    512 (256^2 x 32)           6023 / 5535 / 5561 / 5601 / 5756
+//   1024 (256^2 x 64, sparse)   8265 / 7511 / 7328 / 7325 / 7461
+//   8192 (512^2 x 128)         42916 / 42898 (42589 in 2) / 43636
+int bpT_parts(const KParams &k) {
+    const long long full = k.n_valid / ((long long)kT * kT * 16);
+    return full < 60 ? 32 : (full < 250 ? 16 : (full < 1500 ? 8 : (full < 6000 ? 4 : 2)));
+}
+
 template <int KZ, bool DET>
 void launch_bpT(const KParams &k, hipStream_t s, const float *gvol, void *gFout, const double *fscale) {
-    const dim3 grid((unsigned)k.bp_tiles_x, (unsigned)k.bp_tiles_y, (unsigned)(k.n_pitches * k.bp_runs));
+    const int parts = bpT_parts(k);
+    const dim3 grid((unsigned)k.bp_tiles_x, (unsigned)k.bp_tiles_y, (unsigned)(k.n_pitches * k.bp_runs * parts));
     const BpArgs a = bp_args(k);
     const uint2 *boxes = reinterpret_cast<const uint2 *>(k.boxes);
     const float4 *rays = reinterpret_cast<const float4 *>(k.tref);
@@ -390,7 +399,7 @@ void launch_bpT(const KParams &k, hipStream_t s, const float *gvol, void *gFout,
     const BpTShape shape = bpT_shape<KZ, DET>(k, fb, bytes);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(kNT), bytes, s, a, gvol, gFout, fscale, k.rows, k.cols, k.first_view,
-                           k.view, boxes, rays, series, shape);
+                           k.view, boxes, rays, series, shape, parts);
     };
     if (fb) go(k_bpT_lds<KZ, true, DET, 66>);
     else if (shape.pitch == 34) go(k_bpT_lds<KZ, false, DET, 34>);
