@@ -51,6 +51,9 @@ __device__ inline unsigned long long to_fixed(float v, double S) {
     return (unsigned long long)__double2ll_rn((double)v * S);
 }
 
+// max(0, 1 - |d|)
+__device__ inline float hat(float d) { return med3(1.0f - fabsf(d), 0.0f, 1.0f); }
+
 // FB: some box of the plan may exceed the LDS tile; those views scatter their taps
 // straight into g^F-bar with global atomics (the cells the forward's HBM path reads).
 //
@@ -74,7 +77,7 @@ __device__ inline unsigned long long to_fixed(float v, double S) {
 // integer atomics); S = *fscale, a power of two chosen from max |fbar| so that no sum can
 // reach 2^62.  Integer sums do not depend on their order: the result is the same bits on
 // every run.
-template <int KZ, bool FB, bool DET, int PITCH>
+template <int KZ, bool FB, bool DET, int PITCH, bool WIN>
 __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *__restrict__ gFout,
                          const double *__restrict__ fscale, int rows, int cols, long long first_view,
                          const float4 *__restrict__ view_tab, const uint2 *__restrict__ box_tab,
@@ -93,8 +96,13 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int ix = bxi * kT + (tid & (kT - 1));
-    const int iy = byi * kT + (tid >> 4);
+    // A wave takes 16 x 4 neighbouring voxel columns, with WIN every second one of the tile in x and
+    // y: its lanes then spread over the whole box, where neighbours would meet up to eight at a time
+    // in one column's cells (see the walks below).
+    const int tx = WIN ? 2 * (lane & 7) + (wave & 1) : tid & (kT - 1);
+    const int ty = WIN ? 2 * (lane >> 3) + (wave >> 1) : tid >> 4;
+    const int ix = bxi * kT + tx;
+    const int iy = byi * kT + ty;
     const int part = bz % parts;
     const int pitch = bz / parts / p.runs;
     const int run = bz / parts % p.runs;
@@ -108,8 +116,9 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
 
     // register r of a lane holds slice (r + off) mod KZ: lanes of a wave that lie on one ray
     // then scatter slices of different z (different detector rows) in the same instruction
-    const int off = ((tid & 15) + 4 * ((tid >> 4) & 3)) & (KZ - 1);
+    const int off = WIN ? 0 : ((tid & 15) + 4 * ((tid >> 4) & 3)) & (KZ - 1);
     float A[KZ], B[KZ], fb[KZ];
+    bool tame = true;              // no cotangent that is not finite or whose weights might not be
     int wlo = INT_MAX, whi = INT_MIN;
     int g_alo[NG], g_ahi[NG], g_flo[NG], g_fhi[NG];
 #pragma unroll
@@ -129,6 +138,7 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
                     A[r] = e.li - 0.5f;
                     B[r] = e.lo + 0.5f;
                     fb[r] = ldg(fvol + ((size_t)(iz0 + jj) * p.ny + iy) * p.nx + ix) * p.scale;
+                    tame = tame && fabsf(fb[r]) < 1e30f;
                     alo = min(alo, e.nf);
                     ahi = max(ahi, e.nl);
                     flo = max(flo, (int)ceilf(A[r] + 1.0f) + 1);
@@ -169,9 +179,16 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
     }
     __syncthreads();
 
+    // (the window's rows of weight 0 take part in its sums, so a NaN or infinity would spread to
+    // them, also beyond the box: such a wave walks slice by slice)
+    const bool calm = WIN && __ballot(!tame) == 0;
+    // half-diagonal of the tile's voxel columns
+    const float wh = 0.5f * (kT - 1) * sqrtf(p.dx * p.dx + p.dy * p.dy) * 1.0001f;
+    // lane s < KZ: its slice's distance from the middle one
+    const float smid = (float)((lane & (KZ - 1)) - KZ / 2);
     // offsets from the tile centre (half-integers of the grid steps)
-    const float ddx = ((float)(tid & (kT - 1)) - 0.5f * (kT - 1)) * p.dx;
-    const float ddy = ((float)(tid >> 4) - 0.5f * (kT - 1)) * p.dy;
+    const float ddx = ((float)tx - 0.5f * (kT - 1)) * p.dx;
+    const float ddy = ((float)ty - 0.5f * (kT - 1)) * p.dy;
     const float zoff = (float)j0 * p.dz;
     const uint2 *__restrict__ boxes =
         box_tab + ((size_t)(run * p.tiles_y + byi) * p.tiles_x + bxi) * p.W;
@@ -234,11 +251,76 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
         const float mf = (float)m;
         const unsigned word = (unsigned)__ballot(m >= bound);
         const unsigned active = word & ~(word >> NG), full = (word >> (2 * NG)) & ~(word >> (3 * NG));
-        // the view's active slices in register order: each slice adds its row weights to
-        // two pending rows (R, R+1) kept in registers; a row's two taps (columns c0, c0+1)
-        // are scattered once the walk has moved past it, so slices that share detector
-        // rows (row steps of 0 or 1) meet in registers first
-        auto walk = [&](auto emit) {
+        // register r's weight (its cotangent over v*, times its coverage) and detector row
+        auto weight = [&](int r, bool inside) {
+            float a = vinv * fb[r];
+            if (!inside) a *= med3(fminf(mf - A[r], B[r] - mf), 0.0f, 1.0f);
+            return a;
+        };
+        auto rowpos = [&](int r) { return med3(fmaf((float)((r + off) & (KZ - 1)), st, rb), 0.0f, rmax); };
+        // WIN.  Rows advance by nearly the same step per slice in all lanes of a wave: measured from the
+        // row of its middle slice, slice s of any lane lies in rows k_s .. k_s + 3 with k_s the
+        // same for the wave, as long as the steps' spread over the wave times KZ / 2 stays below 1
+        // (the tile's voxels are within wh of its centre, at distance rho_c).  The walk then keeps
+        // those four rows' sums in registers, each slice adding its hat-function weights to them,
+        // and scatters a row (two columns) when the window leaves it: one branch for the wave, all
+        // lanes at once, each row once.
+        const float rw = sqrtf(ray.w);
+        const float shi = p.q_scale * p.dz * __builtin_amdgcn_rcpf(rw - wh);
+        const float slo = p.q_scale * p.dz * __builtin_amdgcn_rcpf(rw + wh);
+        const bool narrow = calm && __builtin_amdgcn_readfirstlane((int)(rw > 2.0f * wh && (shi - slo) * (0.5f * KZ) < 0.99f && slo > 0.0f));
+        const float mid = floorf(fmaf((float)(KZ / 2), st, rb));
+        auto window = [&](auto emit) {                        // emit(rows past mid, the row's sum)
+            // floor((s - KZ / 2) times the least or largest step)
+            const int kv = (int)floorf(smid * (smid < 0.0f ? shi : slo) - 1e-3f);
+            const unsigned on = active & ((1u << NG) - 1u);
+            if (!on) return;
+            float W0 = 0.0f, W1 = 0.0f, W2 = 0.0f, W3 = 0.0f;
+            int k = __builtin_amdgcn_readlane(kv, kKG * __builtin_ctz(on));
+            float rel = mid + (float)k;                       // the lane's row of W0
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (!(active & (1u << g))) continue;
+                const bool inside = full & (1u << g);
+#pragma unroll
+                for (int s = g * kKG; s < g * kKG + kKG; ++s) {
+                    const int ks = __builtin_amdgcn_readlane(kv, s);
+                    const float a = weight(s, inside);
+                    const float rr = rowpos(s);
+                    if (ks != k) {
+                        // rows that the window leaves; past four of them it is empty
+                        for (int n = min(ks - k, 4) - 1; n > 0; --n) {
+                            emit(k, W0);
+                            W0 = W1;
+                            W1 = W2;
+                            W2 = W3;
+                            W3 = 0.0f;
+                            ++k;
+                        }
+                        emit(k, W0);
+                        W0 = W1;
+                        W1 = W2;
+                        W2 = W3;
+                        W3 = 0.0f;
+                        k = ks;
+                        rel = mid + (float)k;
+                    }
+                    const float d = rr - rel;
+                    W0 = fmaf(a, hat(d), W0);
+                    W1 = fmaf(a, hat(d - 1.0f), W1);
+                    W2 = fmaf(a, hat(d - 2.0f), W2);
+                    W3 = fmaf(a, hat(d - 3.0f), W3);
+                }
+            }
+            emit(k, W0);
+            emit(k + 1, W1);
+            emit(k + 2, W2);
+            emit(k + 3, W3);
+        };
+        // Otherwise slice by slice: each adds its row weights to two pending rows (R, R+1) kept in
+        // registers; a row's two taps (columns c0, c0+1) are scattered once the walk has moved past
+        // it, so slices that share detector rows (row steps of 0 or 1) meet in registers first
+        auto walk = [&](auto emit) {                          // emit(row of the box, its sum)
             int R = -1;                                       // -1: nothing pending yet
             float P = 0.0f, Q = 0.0f;
 #pragma unroll
@@ -246,12 +328,9 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
                 if (!(active & (1u << g))) continue;
                 const bool inside = full & (1u << g);
 #pragma unroll
-                for (int s = 0; s < kKG; ++s) {
-                    const int r = g * kKG + s;                // register
-                    const float sl = (float)((r + off) & (KZ - 1));     // its slice
-                    float a = vinv * fb[r];
-                    if (!inside) a *= med3(fminf(mf - A[r], B[r] - mf), 0.0f, 1.0f);
-                    const float rr = med3(fmaf(sl, st, rb), 0.0f, rmax);
+                for (int s = g * kKG; s < g * kKG + kKG; ++s) {
+                    const float a = weight(s, inside);
+                    const float rr = rowpos(s);
                     const int Rk = (int)rr;
                     const float a1 = a * __builtin_amdgcn_fractf(rr), a0 = a - a1;   // rows Rk, Rk+1
                     const bool same = Rk == R, next = Rk == R + 1;
@@ -267,13 +346,13 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
                 emit(R + 1, Q);
             }
         };
+        const int midrow = (int)mid;
         if (fits(b)) {
-            // LDS addresses in 32 bits (the box is shared memory)
+            // LDS addresses in 32 bits (the box is shared memory); a row of all lanes at once
             LdsAcc *bx = box + buf * cells + c0;
-            walk([&](int row, float v) {
+            auto put = [&](LdsAcc *cell, float v) {
                 if (v != 0.0f) {
                     const float v1 = v * tc;
-                    LdsAcc *cell = bx + __mul24(row, pitch_a);
                     if constexpr (DET) {
                         const unsigned long long q = to_fixed(v, fx), q1 = to_fixed(v1, fx);
                         __hip_atomic_fetch_add(cell, q - q1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -285,7 +364,13 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
                                                __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                 }
-            });
+            };
+            if (WIN && narrow) {
+                LdsAcc *at = bx + midrow * pitch_a;
+                window([&](int k, float v) { put(at + k * pitch_a, v); });
+            } else {
+                walk([&](int row, float v) { put(bx + __mul24(row, pitch_a), v); });
+            }
         } else {
             // rows and columns relative to the box, which is clipped to the zero-padded
             // detector; cells of the padding are dropped (the forward reads zeros there)
@@ -314,7 +399,7 @@ __device__ void bpT_tile(const BpArgs p, const float *__restrict__ fvol, void *_
     if (mlo <= mhi && fits(prev_b)) flush(mhi, prev_b, (mhi - mlo) & 1);
 }
 
-template <int KZ, bool FB, bool DET, int PITCH>
+template <int KZ, bool FB, bool DET, int PITCH, bool WIN>
 __global__ __launch_bounds__(kNT) void k_bpT_lds(BpArgs p, const float *__restrict__ fvol,
                                                  void *__restrict__ gFout,
                                                  const double *__restrict__ fscale, int rows,
@@ -325,7 +410,7 @@ __global__ __launch_bounds__(kNT) void k_bpT_lds(BpArgs p, const float *__restri
                                                  BpTShape shape, int parts) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ int red[8];
-    bpT_tile<KZ, FB, DET, PITCH>(p, fvol, gFout, fscale, rows, cols, first_view, view_tab, box_tab, ray_tab, series,
+    bpT_tile<KZ, FB, DET, PITCH, WIN>(p, fvol, gFout, fscale, rows, cols, first_view, view_tab, box_tab, ray_tab, series,
                           shape, parts, blockIdx.x, blockIdx.y, blockIdx.z, lds, red);
 }
 
@@ -386,6 +471,14 @@ int bpT_parts(const KParams &k) {
     return full < 60 ? 32 : (full < 250 ? 16 : (full < 1500 ? 8 : (full < 6000 ? 4 : 2)));
 }
 
+// Whether the rows' sums are kept in a window common to the wave (WIN).  It takes half of the LDS
+// atomics' instructions and fewer operations, but its lanes reach one column's cells together
+// where the slice-by-slice walk has turned their slices against each other, so it pays only where
+// boxes are wide enough to keep the lanes apart: whole adjoint, walk / window, 512^2 x 10 network pitch
+// (boxes 20 x 57) 2.22 / 1.66 ms, 256^2 x 32 (40 x 79) 5.54 / 5.20, 128^2 x 8 (20 x 217) 0.51 / 0.40,
+// clinical (32 x 44) 42.7 / 47.7, 256^2 x 64 sparse (49 x 25) 7.3 / 13.0.
+bool bpT_window(const KParams &k) { return k.bp_box_cols > 50; }
+
 template <int KZ, bool DET>
 void launch_bpT(const KParams &k, hipStream_t s, const float *gvol, void *gFout, const double *fscale) {
     const int parts = bpT_parts(k);
@@ -401,10 +494,11 @@ void launch_bpT(const KParams &k, hipStream_t s, const float *gvol, void *gFout,
         hipLaunchKernelGGL(kernel, grid, dim3(kNT), bytes, s, a, gvol, gFout, fscale, k.rows, k.cols, k.first_view,
                            k.view, boxes, rays, series, shape, parts);
     };
-    if (fb) go(k_bpT_lds<KZ, true, DET, 66>);
-    else if (shape.pitch == 34) go(k_bpT_lds<KZ, false, DET, 34>);
-    else if (shape.pitch == 66) go(k_bpT_lds<KZ, false, DET, 66>);
-    else go(k_bpT_lds<KZ, false, DET, 0>);
+    if (fb) go(k_bpT_lds<KZ, true, DET, 66, false>);
+    else if (shape.pitch == 34) go(k_bpT_lds<KZ, false, DET, 34, false>);
+    else if (shape.pitch == 66 && !bpT_window(k)) go(k_bpT_lds<KZ, false, DET, 66, false>);
+    else if (shape.pitch == 66) go(k_bpT_lds<KZ, false, DET, 66, true>);
+    else go(k_bpT_lds<KZ, false, DET, 0, true>);
 }
 
 template <bool DET>

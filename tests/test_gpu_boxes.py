@@ -75,3 +75,33 @@ def test_splits(nxy, nz):
     other = K.filter_views(ref_plan, sino * 2)
     both = K.backproject_batch([plan, plan], [gF, other])
     assert torch.equal(both[0], vol) and torch.equal(both[1], K.backproject(plan, other))
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 3.0e38])
+def test_adjoint_of_values_that_are_not_finite(bad):
+    """One voxel's cotangent not finite, or near the largest float: views that none of its tile's
+    voxels see are unchanged, and a finite one is the float64 transpose's."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = configs.tiny(nxy=20, nz=14, cols=100, rows=12, views_per_turn=72, turns=3, feed=24.0, dxy=2.0,
+                      slices_per_pitch=12)
+    geom, gr = wl.geom.as_dict(), wl.grid.as_dict()
+    plan = K.Plan(geom, gr, device=0)
+    y = np.random.default_rng(3).normal(size=(14, 20, 20)).astype(np.float32)
+    clean = y.copy()
+    clean[7, 4, 9] = 0.0
+    y[7, 4, 9] = bad
+    got = K.recon_backward(plan, torch.from_numpy(y).cuda()).cpu().numpy()
+    if np.isfinite(bad):
+        ref = O.recon_T(O.Scan(geom), gr, y.astype(np.float64))
+        err = np.linalg.norm(got / 1e30 - ref / 1e30) / np.linalg.norm(ref / 1e30)
+        print(f"[parity] adjoint of {bad}: {err:.2e}", flush=True)
+        assert err <= 1e-5 + 2.0 ** -23 * 90
+        return
+    base = K.recon_backward(plan, torch.from_numpy(clean).cuda()).cpu().numpy()
+    tile = np.zeros(y.shape)
+    tile[:, :16, :16] = 1.0
+    seen = (O.recon_T(O.Scan(geom), gr, tile) != 0).any(axis=(1, 2))
+    assert not np.isfinite(got).all() and not seen.all()
+    assert np.array_equal(np.isfinite(got[~seen]), np.ones_like(got[~seen], dtype=bool))
+    assert np.allclose(got[~seen], base[~seen], atol=1e-5 * np.abs(base).max())
