@@ -417,7 +417,10 @@ static void set_workspace(PlanHost &P) {
     const uint64_t rc = (uint64_t)g.det_rows * g.det_cols;
     const uint64_t per_view = (uint64_t)(P.n_psi + g.det_rows) * g.det_cols * 4;
     P.chunk_views = std::min<int64_t>(nfilt, std::max<int64_t>(kFilterChunk, (int64_t)(kFilterChunkBytes / per_view)));
-    if (P.hil_mode == KATS_HILBERT_MFMA) {
+    // whole rounds of the matrix-core Hilbert's tiles where several chunks are needed anyway; a scan
+    // that fits in one chunk stays whole (a second chunk's launches cost a 64^3 scan of 1078 filtered
+    // views 25 of 166 us and the network pitch's 584 views 40 us forward and backward)
+    if (P.hil_mode == KATS_HILBERT_MFMA && P.chunk_views < nfilt) {
         const int64_t round = (int64_t)kHilTileRows * kHilBlocks;
         const int64_t rounds = P.chunk_views * P.n_psi / round;
         if (rounds >= 1) P.chunk_views = std::min<int64_t>(P.chunk_views, rounds * round / P.n_psi);
