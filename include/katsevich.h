@@ -302,7 +302,7 @@ int katsevich_add_noise(const float *d_in, float *d_out, uint64_t n, const float
 /* d_result[0] = RMSE = sqrt(sum (f - ref)^2 / n); d_result[1] = SSIM of the two whole
  * images (one window): (2 mu_f mu_r + c1)(2 cov + c2) / ((mu_f^2 + mu_r^2 + c1)(var_f +
  * var_r + c2)), population moments, c1 = (0.01 (max ref - min ref))^2, c2 = (0.03 (max
- * ref - min ref))^2 (Sec. IV).  Float64 accumulation, two passes, deterministic. */
+ * ref - min ref))^2 (Sec. IV).  Float64 accumulation, one pass, deterministic. */
 int katsevich_rmse_ssim(const float *d_f, const float *d_ref, uint64_t n, double *d_result,
                         void *d_scratch, uint64_t scratch_bytes, void *stream);
 
