@@ -343,6 +343,13 @@ int katsevich_conv3_grad(const float *d_x, const int64_t *x_strides, const float
                          const int64_t *y_strides, const int64_t *shape, float *d_dw, float *d_db,
                          void *d_scratch, uint64_t scratch_bytes, void *stream);
 
+/* The three depth-shifted copies of x [batch][channel][depth] planes side by side as channels, zeros
+ * beyond both ends: d_out [batch][depth][3][channel][height][width], copy k of depth d holding depth
+ * d + k - 1 (shape: batch, channels, depth, height, width; strides as above).  A 2-D convolution of
+ * d_out is the 3-D one of x. */
+int katsevich_stack3(const float *d_x, const int64_t *x_strides, float *d_out, const int64_t *shape,
+                     void *stream);
+
 /* Gradients of PReLU (x > 0 ? x : slope[c] x) on [batch][channel][depth] planes of height x width
  * dense samples (shape: batch, channels, depth, height, width; strides as above): d_dx and d_dslope
  * [channels] from the input x and the gradient dy of the output.  d_scratch:

@@ -631,6 +631,30 @@ int katsevich_conv3_grad(const float *d_x, const int64_t *x_strides, const float
     return KATS_OK;
 }
 
+int katsevich_stack3(const float *d_x, const int64_t *x_strides, float *d_out, const int64_t *shape, void *stream) {
+    g_err.clear();
+    if (!d_x || !x_strides || !d_out || !shape) return fail(KATS_EINVAL, "katsevich_stack3: null argument");
+    int64_t planes = 1;
+    for (int i = 0; i < 5; ++i) {
+        if (shape[i] < 1 || shape[i] > INT32_MAX)
+            return fail(KATS_EINVAL, "katsevich_stack3: a size is not in 1 .. 2^31 - 1");
+        if (i < 3 && (planes *= shape[i]) > INT32_MAX) return fail(KATS_EINVAL, "katsevich_stack3: volume too large");
+    }
+    // offsets are 64 bits; the whole output stays below 2^62 bytes
+    if (shape[3] * shape[4] > (((int64_t)1 << 58) / planes)) return fail(KATS_EINVAL, "katsevich_stack3: volume too large");
+    kats::Stack3Args a{};
+    a.x = d_x;
+    a.out = d_out;
+    for (int i = 0; i < 3; ++i) a.xs[i] = x_strides[i];
+    a.B = (int)shape[0];
+    a.C = (int)shape[1];
+    a.D = (int)shape[2];
+    a.n = shape[3] * shape[4];
+    const hipError_t e = kats::launch_stack3(a, static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "katsevich_stack3: launch");
+    return KATS_OK;
+}
+
 static int prelu_shape(const int64_t *shape, uint64_t &blocks) {
     if (!shape) return fail(KATS_EINVAL, "katsevich_prelu_grad: null argument");
     uint64_t planes = 1;

@@ -134,6 +134,17 @@ hipError_t launch_conv3(Conv3Args a, hipStream_t s);
 // part: kConv3Blocks * kConv3Part floats
 hipError_t launch_conv3_wgrad(Conv3Args a, const float *dy, float *dw, float *db, float *part, hipStream_t s);
 
+// depth-shifted copies of [batch][channel][depth] planes of n dense samples (strides xs in floats)
+// as channels: out [batch][depth][3 channel][n]
+struct Stack3Args {
+    const float *x;
+    float *out;
+    long long xs[3];
+    int B, C, D;
+    long long n;
+};
+hipError_t launch_stack3(const Stack3Args &a, hipStream_t s);
+
 // PReLU gradient on [batch][channel][depth] planes of n dense samples (strides of the three in floats)
 struct PreluArgs {
     const float *x, *dy, *slope;

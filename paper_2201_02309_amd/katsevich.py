@@ -82,7 +82,7 @@ EXPORTED = ["katsevich_plan", "katsevich_plan_query", "katsevich_plan_bind",
             "katsevich_sparse_upsample", "katsevich_data_scratch_bytes", "katsevich_max",
             "katsevich_add_noise", "katsevich_rmse_ssim", "katsevich_rmse_ssim_noscratch",
             "katsevich_conv3", "katsevich_conv3_grad", "katsevich_conv3_scratch_bytes",
-            "katsevich_prelu_grad", "katsevich_prelu_scratch_bytes"]
+            "katsevich_prelu_grad", "katsevich_prelu_scratch_bytes", "katsevich_stack3"]
 
 _lib = None
 
@@ -144,6 +144,8 @@ def load_library(path: str = LIB_PATH):
                                          c_void_p, POINTER(c_int64), c_void_p, POINTER(c_int64), c_void_p,
                                          c_uint64, c_void_p]
     lib.katsevich_prelu_grad.restype = c_int
+    lib.katsevich_stack3.argtypes = [c_void_p, POINTER(c_int64), c_void_p, POINTER(c_int64), c_void_p]
+    lib.katsevich_stack3.restype = c_int
     lib.katsevich_plan_destroy.argtypes = [c_void_p]
     lib.katsevich_plan_destroy.restype = None
     lib.katsevich_status_string.argtypes = [c_int]
@@ -559,6 +561,19 @@ def conv3_grad(x, dy, weight_shape):
             (c_int64 * 6)(B, cin, weight_shape[0], D, H, W), c_void_p(dw.data_ptr()), c_void_p(db.data_ptr()),
             c_void_p(part.data_ptr()), c_uint64(part.numel()), _stream_handle(x.device)))
     return dw, db
+
+
+def stack3(x):
+    """katsevich_stack3: x [B, C, D, H, W] -> [B D, 3 C, H, W], the three depth-shifted copies of x as
+    channels.  x: float32, planes dense."""
+    import torch
+    B, C, D, H, W = x.shape
+    out = torch.empty((B * D, 3 * C, H, W), dtype=torch.float32, device=x.device)
+    lib = load_library()
+    with torch.cuda.device(x.device):
+        _check(lib, lib.katsevich_stack3(c_void_p(x.data_ptr()), _volume_strides(x), c_void_p(out.data_ptr()),
+                                         (c_int64 * 5)(B, C, D, H, W), _stream_handle(x.device)))
+    return out
 
 
 def prelu_grad(x, dy, slope):

@@ -30,7 +30,13 @@ def _conv3x3x3(x, weight, bias):
     xp = F.pad(x, (0, 0, 0, 0, 1, 1))
     stack = torch.cat([xp[:, :, k:k + D] for k in range(3)], dim=1)      # [B, 3C, D, H, W]
     stack = stack.permute(0, 2, 1, 3, 4).reshape(B * D, 3 * C, H, W)
-    cout = weight.shape[0]
+    return _conv_stack(stack, D, weight, bias)
+
+
+def _conv_stack(stack, D, weight, bias):
+    """The 2-D convolution of [B D, 3 C, H, W] depth-shifted copies -> [B, cout, D, H, W]."""
+    (BD, C3, H, W), cout = stack.shape, weight.shape[0]
+    B, C = BD // D, C3 // 3
     w2 = weight.permute(0, 2, 1, 3, 4).reshape(cout, 3 * C, 3, 3)
     y = F.conv2d(stack, w2, bias, padding=1)
     return y.reshape(B, D, cout, H, W).permute(0, 2, 1, 3, 4)
@@ -78,7 +84,8 @@ class _Conv3Fn(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, weight, bias):
         ctx.save_for_backward(x, weight)
-        return _conv3x3x3(x, weight, bias)
+        stack = _K.stack3(x if _K.rows_dense(x) else x.contiguous())
+        return _conv_stack(stack, x.shape[2], weight, bias)
 
     @staticmethod
     def backward(ctx, gy):

@@ -127,3 +127,23 @@ def test_prelu_gradients(shape):
     v = x.detach().requires_grad_()
     gx = torch.autograd.grad((m(v) ** 2).sum(), v, create_graph=True)[0]
     assert torch.isfinite(torch.autograd.grad(gx.sum(), v)[0]).all()
+
+
+# planes of whole vectors, of a remainder, one sample; unaligned; strided as the layers store them
+@pytest.mark.parametrize("shape", [(2, 3, 1, 4, 4), (1, 16, 2, 8, 32), (2, 5, 7, 65, 31), (1, 1, 1, 1, 1),
+                                   (3, 4, 5, 130, 66)])
+@pytest.mark.parametrize("layout", ["dense", "depth first", "shifted"])
+def test_depth_copies(shape, layout):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B, C, D, H, W = shape
+    if layout == "depth first":
+        x = torch.randn(B, D, C, H, W, device="cuda").permute(0, 2, 1, 3, 4)
+    else:
+        off = 1 if layout == "shifted" else 0
+        x = torch.randn(B * C * D * H * W + off, device="cuda")[off:].view(shape)
+    x[0, 0, 0, 0, 0] = float("nan")
+    xp = torch.nn.functional.pad(x, (0, 0, 0, 0, 1, 1))
+    want = torch.stack([xp[:, :, k:k + D] for k in range(3)], 1).permute(0, 3, 1, 2, 4, 5).reshape(B * D, 3 * C, H, W)
+    got = N._K.stack3(x)
+    assert torch.equal(got.view(torch.int32), want.contiguous().view(torch.int32))
