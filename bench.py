@@ -183,7 +183,7 @@ def data_path_bench(sino, vol, ref_vol, reps=5):
         "max": (lambda: K.max_value(up, scratch=scratch, out=d_max), 4 * n),
         "add_noise": (lambda: K.add_noise(up, 1e5, 0.5, 7, d_max=d_max, out=noisy), 8 * n),
         "rmse_ssim": (lambda: K.rmse_ssim(vol, ref_vol, scratch=scratch, result=res),
-                      2 * 2 * 4 * vol.numel()),
+                      2 * 4 * vol.numel()),
     }
     out = {"workload": f"clinical sinogram {tuple(sino.shape)} float32, sparse step {step}; "
                        f"metrics on the {tuple(vol.shape)} volume",

@@ -138,7 +138,8 @@ typedef struct katsevich_plan_info {
                                           (-1: library atan2f) */
     int32_t bp_slices;                 /* slices per backprojection register run */
     int32_t bp_box_rows, bp_box_cols;  /* largest detector footprint box of a backprojection
-                                          tile; boxes up to 32 x 64 are staged in LDS, a plan
+                                          tile; boxes up to 96 x 48 or 48 x 128 (at bp_slices 8
+                                          and 32: 32 x 64 and 64 x 64) are staged in LDS, a plan
                                           with larger ones uses the kernel with an HBM path */
     int32_t half_sample;               /* 1 with KATS_FLAG_HALF_SAMPLE_DERIVATIVE: first_view,
                                           last_view, window_lo and the g^F views then count
@@ -251,8 +252,8 @@ int katsevich_backproject(katsevich_plan_t plan, const float *d_gF, float *d_vol
  * (katsevich_filter output of plans[i]) into d_vol[i], exactly as katsevich_backproject
  * would (bit-identical results).  One launch covers the (pitch, slice run, tile) tasks of
  * up to 16 items, so reconstructions of different sizes, pitches and grids fill the GPU
- * together; items whose footprint boxes all fit the kernel's LDS tile are grouped apart
- * from the others (see bp_box_rows / bp_box_cols of katsevich_plan_info).  All plans
+ * together; items whose footprint boxes take different LDS tiles, or whose size is split in
+ * another way, are grouped apart (see bp_box_rows / bp_box_cols of katsevich_plan_info).  All plans
  * must be bound and use the same bp_slices.  No device memory besides the arrays named;
  * the host arrays may be reused when the call returns.  Asynchronous on stream.
  * Errors: KATS_EINVAL, KATS_ENOTBOUND, KATS_EHIP. */

@@ -98,7 +98,6 @@ KParams make_params(const PlanHost &P) {
     k.bp_tiles_y = P.bp_tiles_y;
     k.bp_runs = P.bp_runs;
     k.bp_kz = P.bp_kz;
-    k.bp_all_fit = P.bp_box_rows <= (P.bp_kz >= 32 ? 2 : 1) * kBpBoxRows && P.bp_box_cols <= kBpBoxCols;
     k.n_valid = P.n_valid;
     k.bp_box_rows = P.bp_box_rows;
     k.bp_box_cols = P.bp_box_cols;

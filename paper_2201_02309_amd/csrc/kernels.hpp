@@ -46,7 +46,6 @@ struct KParams {
     const BpBox *boxes;
     const TileRay *tref;
     int bp_tiles_x, bp_tiles_y, bp_runs, bp_kz;
-    int bp_all_fit;                    // every footprint box fits the LDS tile
     int bp_box_rows, bp_box_cols;      // largest footprint box
     long long n_valid;                 // reconstructed voxels
     int gf_rows, gf_cols;              // padded g^F view (zero border kPad)

@@ -33,8 +33,8 @@ constexpr int kBpKZ = 16;
 // Rows / columns of zero padding around every filtered view g^F (so that clamped
 // bilinear taps outside the detector read exact zeros).
 constexpr int kPad = 2;
-// Largest footprint box the backprojector stages in LDS (rows x columns); a plan whose
-// boxes all fit lets the kernel drop its HBM fallback path.
+// LDS box (rows x columns) of the adjoint backprojector's instance with the HBM path, which plans
+// take whose largest footprint box does not fit the LDS twice.
 constexpr int kBpBoxRows = 32;
 constexpr int kBpBoxCols = 64;
 // Views per chunk of the filter chains: as many as kFilterChunkBytes of intermediates
