@@ -376,7 +376,9 @@ __global__ __launch_bounds__(kNT * TEAMS, TEAMS > 1 ? 1 : bp_waves(KZ, FB, SH::k
                                                 const uint2 *__restrict__ box_tab, int lds_rows) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int red[8];
-    bp_tile<KZ, SH, FB, P4, SUB, TEAMS>(p, gF, vol, view_tab, box_tab, blockIdx.x, blockIdx.y, blockIdx.z, lds_rows, smem, red);
+    const unsigned tiles = gridDim.x * gridDim.y;
+    const TileAt t = xcd_tile(kXcdForward, gridDim.x, gridDim.y, blockIdx.x + gridDim.x * blockIdx.y, blockIdx.z, tiles * blockIdx.z);
+    bp_tile<KZ, SH, FB, P4, SUB, TEAMS>(p, gF, vol, view_tab, box_tab, t.x, t.y, blockIdx.z, lds_rows, smem, red);
 }
 
 // ---------------------------------------------------------------------------------
@@ -411,12 +413,10 @@ __global__ __launch_bounds__(kNT * TEAMS, TEAMS > 1 ? 1 : bp_waves(KZ, FB, SH::k
     int r = 0;
     while (r + 1 < g.n && g.r[r + 1].first_task <= task) ++r;
     const BpRequest &q = g.r[r];
-    long long local = task - q.first_task;
-    const int bxi = (int)(local % q.a.tiles_x);
-    local /= q.a.tiles_x;
-    const int byi = (int)(local % q.a.tiles_y);
-    const int bz = (int)(local / q.a.tiles_y);
-    bp_tile<KZ, SH, FB, P4, SUB, TEAMS>(q.a, q.gF, q.vol, q.view, q.boxes, bxi, byi, bz, lds_rows, smem, red);
+    const unsigned local = (unsigned)(task - q.first_task), tiles = (unsigned)q.a.tiles_x * (unsigned)q.a.tiles_y;
+    const unsigned bz = local / tiles, l = local - bz * tiles;
+    const TileAt t = xcd_tile(kXcdForward, q.a.tiles_x, q.a.tiles_y, l, bz, (unsigned)task - l);
+    bp_tile<KZ, SH, FB, P4, SUB, TEAMS>(q.a, q.gF, q.vol, q.view, q.boxes, t.x, t.y, (int)bz, lds_rows, smem, red);
 }
 
 }  // namespace

@@ -410,8 +410,10 @@ __global__ __launch_bounds__(kNT) void k_bpT_lds(BpArgs p, const float *__restri
                                                  BpTShape shape, int parts) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ int red[8];
+    const unsigned tiles = gridDim.x * gridDim.y;
+    const TileAt t = xcd_tile(kXcdAdjoint, gridDim.x, gridDim.y, blockIdx.x + gridDim.x * blockIdx.y, blockIdx.z, tiles * blockIdx.z);
     bpT_tile<KZ, FB, DET, PITCH, WIN>(p, fvol, gFout, fscale, rows, cols, first_view, view_tab, box_tab, ray_tab, series,
-                          shape, parts, blockIdx.x, blockIdx.y, blockIdx.z, lds, red);
+                          shape, parts, t.x, t.y, blockIdx.z, lds, red);
 }
 
 // Whether the odd series serves every voxel's angle from its tile centre's ray: a voxel lies

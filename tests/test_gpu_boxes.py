@@ -105,3 +105,42 @@ def test_adjoint_of_values_that_are_not_finite(bad):
     assert not np.isfinite(got).all() and not seen.all()
     assert np.array_equal(np.isfinite(got[~seen]), np.ones_like(got[~seen], dtype=bool))
     assert np.allclose(got[~seen], base[~seen], atol=1e-5 * np.abs(base).max())
+
+
+# tiles of a layer: 528 = 16 * 33 and 567 (ragged rows), where the forward's order by XCD begins, and
+# 1023, 1056, 1089 around the adjoint's; slices of one and of two layers
+@pytest.mark.parametrize("nx,ny,nz", [(520, 256, 5), (330, 432, 20), (528, 490, 5), (513, 505, 5), (520, 513, 18)])
+def test_tile_order(nx, ny, nz):
+    """Many tiles, in whatever order their blocks take them, against the same voxels in grids of few
+    tiles: every voxel written, the adjoint the sum of the parts' adjoints."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = configs.tiny(nxy=40, nz=nz, cols=96, rows=16, views_per_turn=72, turns=4, feed=24.0, dxy=2.0,
+                      slices_per_pitch=12)
+    geom, gr = wl.geom.as_dict(), wl.grid.as_dict()
+    d = 80.0 / max(nx, ny)
+    gr.update(nx=nx, ny=ny, dx=d, dy=d, x_first=-d * (nx - 1) / 2, y_first=-d * (ny - 1) / 2)
+    print(f"[case] {nx} x {ny} x {nz}", flush=True)
+    plan = K.Plan(geom, gr, device=0)
+    torch.manual_seed(0)
+    sino = torch.rand(geom["n_views"], geom["det_rows"], geom["det_cols"], device="cuda")
+    y = torch.randn(nz, ny, nx, device="cuda")
+    vol = K.recon(plan, sino, out=torch.full((nz, ny, nx), float("nan"), device="cuda"))
+    gsino = K.recon_backward(plan, y)
+    two = torch.full((2, nz, ny, nx), float("nan"), device="cuda")
+    gF = K.filter_views(plan, sino)
+    K.backproject_batch([plan, plan], [gF, gF], vols=[two[0], two[1]])
+    assert torch.equal(two[0], vol) and torch.equal(two[1], vol)
+    ref, gref = torch.empty_like(vol), torch.zeros_like(gsino, dtype=torch.float64)
+    for j in range(0, ny, 176):
+        for i in range(0, nx, 176):
+            m, n = min(176, ny - j), min(176, nx - i)
+            part = K.Plan(geom, dict(gr, nx=n, ny=m, x_first=gr["x_first"] + i * d, y_first=gr["y_first"] + j * d),
+                          device=0)
+            ref[:, j:j + m, i:i + n] = K.recon(part, sino)
+            gref += K.recon_backward(part, y[:, j:j + m, i:i + n].contiguous()).double()
+            part.close()
+    # two float32 results, each within the parity bar of 1e-5
+    assert bool(torch.isfinite(vol).all())
+    assert float((vol - ref).double().norm() / ref.double().norm()) <= 2e-5
+    assert float((gsino.double() - gref).norm() / gref.norm()) <= 2e-5 + 2.0 ** -22 * plan.info["bp_box_cols"]
