@@ -176,8 +176,9 @@ __global__ __launch_bounds__(kCT, 2) void k_conv3(Conv3Args a) {
 // (output channel x input channel).  dy comes straight from memory (one load per 27 products), x
 // from the LDS planes (a row's samples serve three taps).  CS = 4 (mod 64): a wave reads 16
 // channels x 4 columns from different banks.  Workgroups are persistent over (tile, depth range)
-// tasks; a wave's sums are float32 (the bias gradient's float64: it may cancel to nothing), the
-// workgroup's four are added in LDS, the workgroups' in float64.
+// tasks; a wave's sums are float32, the workgroup's four are added in LDS, the workgroups' in float64.
+// The bias gradient may cancel to nothing: it is summed in float64 throughout, its partials stored as
+// two floats.
 __global__ __launch_bounds__(kCT, 2) void k_conv3_wgrad(Conv3Args a, const float *__restrict__ dy,
                                                         float *__restrict__ part) {
     constexpr int CH = 16, CS = 388;
@@ -261,23 +262,27 @@ __global__ __launch_bounds__(kCT, 2) void k_conv3_wgrad(Conv3Args a, const float
             }
         if (lane < 16) {
             dbs[lane] = w ? dbs[lane] + db : db;
-            lds[27 * 256 + lane] = (float)dbs[lane];
+            const float hi = (float)dbs[lane];
+            lds[27 * 256 + lane] = hi;
+            lds[27 * 256 + 16 + lane] = (float)(dbs[lane] - (double)hi);
         }
     }
     __syncthreads();
     for (int e = threadIdx.x; e < kConv3Part; e += kCT) part[(size_t)blockIdx.x * kConv3Part + e] = lds[e];
 }
 
-// dw[co][ci][tap] and db[co] = sums of the workgroups' partials: 16 elements per block, 16 threads
-// each taking every 16th partial in float64.
+// dw[co][ci][tap] and db[co] = sums of the workgroups' partials: 16 elements per block (the bias's 16
+// pairs in the last), 16 threads each taking every 16th partial in float64.
 __global__ __launch_bounds__(kCT) void k_conv3_wsum(const float *__restrict__ part, int np, int cin, int cout,
                                                     float *__restrict__ dw, float *__restrict__ db) {
     __shared__ double sh[16][17];
     const int j = threadIdx.x & 15, g = threadIdx.x >> 4;
-    const int e = blockIdx.x * 16 + j;                 // kConv3Part is a multiple of 16
+    const int e = blockIdx.x * 16 + j;
     double s = 0.0;
 #pragma unroll 8
     for (int p = g; p < np; p += 16) s += (double)part[(size_t)p * kConv3Part + e];
+    if (e >= 27 * 256)
+        for (int p = g; p < np; p += 16) s += (double)part[(size_t)p * kConv3Part + e + 16];
     sh[g][j] = s;
     __syncthreads();
     if (g != 0) return;
@@ -406,7 +411,7 @@ hipError_t launch_conv3_wgrad(Conv3Args a, const float *dy, float *dw, float *db
     const long long tasks = (long long)a.tiles_w * a.tiles_h * a.nseg * a.B;
     const int blocks = (int)(tasks < kConv3Blocks ? tasks : kConv3Blocks);
     hipLaunchKernelGGL(k_conv3_wgrad, dim3(blocks), dim3(kCT), 0, s, a, dy, part);
-    hipLaunchKernelGGL(k_conv3_wsum, dim3(kConv3Part / 16), dim3(kCT), 0, s, (const float *)part, blocks, a.cin,
+    hipLaunchKernelGGL(k_conv3_wsum, dim3(27 * 16 + 1), dim3(kCT), 0, s, (const float *)part, blocks, a.cin,
                        a.cout, dw, db);
     return hipGetLastError();
 }

@@ -126,7 +126,7 @@ struct Conv3Args {
     int B, cin, cout, D, H, W, wm, wk, flip;
     int tiles_w, tiles_h, dseg, nseg;       // set by the launchers
 };
-constexpr int kConv3Part = 27 * 256 + 16;   // floats of one workgroup's weight-gradient partial
+constexpr int kConv3Part = 27 * 256 + 32;   // floats of one workgroup's weight-gradient partial (bias: pairs)
 constexpr int kConv3Blocks = 512;           // its persistent workgroups (two per CU)
 hipError_t launch_conv3(Conv3Args a, hipStream_t s);
 // a: x and the strides of dy in yb, yc, yd; dw [cout][cin][27] and db [cout] (either may be null);

@@ -147,3 +147,19 @@ def test_depth_copies(shape, layout):
     want = torch.stack([xp[:, :, k:k + D] for k in range(3)], 1).permute(0, 3, 1, 2, 4, 5).reshape(B * D, 3 * C, H, W)
     got = N._K.stack3(x)
     assert torch.equal(got.view(torch.int32), want.contiguous().view(torch.int32))
+
+
+@pytest.mark.parametrize("cout,shape", [(1, (1, 10, 256, 256)), (16, (2, 9, 64, 96))])
+def test_bias_gradient_that_cancels(cout, shape):
+    """The sum of a cotangent of either sign is far smaller than its terms: float64 sums, whose
+    errors are 2^-50 of the magnitudes, and one rounding to float32."""
+    m = _conv(2, cout)
+    B, D, H, W = shape
+    for seed in range(4):
+        torch.manual_seed(seed)
+        x = torch.randn(B, 2, D, H, W, device="cuda")
+        g = torch.randn(B, cout, D, H, W, device="cuda")
+        g -= g.double().mean(dim=(0, 2, 3, 4), keepdim=True).float()
+        got = torch.autograd.grad(m(x), m.bias, g)[0].double()
+        want, size = g.double().sum(dim=(0, 2, 3, 4)), g.double().abs().sum(dim=(0, 2, 3, 4))
+        assert bool(((got - want).abs() <= 2.0 ** -24 * want.abs() + 2.0 ** -50 * size).all()), (got - want)
