@@ -62,7 +62,8 @@ def _native_volume(x, channels):
         return False
     B, C, D, H, W = x.shape
     return (B <= 65535 and D <= 4 * 65535 and (16 * D + 1) * H * W <= 1 << 30
-            and B * D * C < 1 << 31 and B * ((H + 7) // 8) * ((W + 31) // 32) < 1 << 31)
+            and B * D * C * ((H * W + 8191) // 8192) < 1 << 24       # workgroups of 256 along x
+            and B * ((H + 7) // 8) * ((W + 31) // 32) < 1 << 31)
 
 
 def _native_conv(x, weight, bias):

@@ -163,3 +163,10 @@ def test_bias_gradient_that_cancels(cout, shape):
         got = torch.autograd.grad(m(x), m.bias, g)[0].double()
         want, size = g.double().sum(dim=(0, 2, 3, 4)), g.double().abs().sum(dim=(0, 2, 3, 4))
         assert bool(((got - want).abs() <= 2.0 ** -24 * want.abs() + 2.0 ** -50 * size).all()), (got - want)
+
+
+def test_launch_limits():
+    """Volumes whose launches would pass 2^32 threads along x stay with torch."""
+    one = torch.empty(1)
+    assert N._native_volume(one.expand(4, 16, 1 << 17, 1, 1), 16)
+    assert not N._native_volume(one.expand(8, 16, 1 << 17, 1, 1), 16)
