@@ -138,7 +138,7 @@ typedef struct katsevich_plan_info {
                                           (-1: library atan2f) */
     int32_t bp_slices;                 /* slices per backprojection register run */
     int32_t bp_box_rows, bp_box_cols;  /* largest detector footprint box of a backprojection
-                                          tile; boxes up to 96 x 48 or 48 x 128 (at bp_slices 8
+                                          tile; boxes up to 64 x 80 or 48 x 128 (at bp_slices 8
                                           and 32: 32 x 64 and 64 x 64) are staged in LDS, a plan
                                           with larger ones uses the kernel with an HBM path */
     int32_t half_sample;               /* 1 with KATS_FLAG_HALF_SAMPLE_DERIVATIVE: first_view,

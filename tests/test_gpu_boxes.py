@@ -144,3 +144,39 @@ def test_tile_order(nx, ny, nz):
     assert bool(torch.isfinite(vol).all())
     assert float((vol - ref).double().norm() / ref.double().norm()) <= 2e-5
     assert float((gsino.double() - gref).norm() / gref.norm()) <= 2e-5 + 2.0 ** -22 * plan.info["bp_box_cols"]
+
+
+# boxes of 65 to 80 columns, at most 48 rows and more
+@pytest.mark.parametrize("rows,box_rows", [(44, 48), (60, 64)])
+def test_box_shapes_of_80_columns(rows, box_rows):
+    test_box_shapes(24, 100, rows, 8, box_rows, 75, 16)
+
+
+def test_batch_of_unlike_boxes():
+    """Requests with few tasks join one launch whatever their boxes: the same bits as alone."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    plans, gFs = [], []
+    for nxy, cols, rows, spp in ((40, 24, 24, 24), (24, 100, 44, 8), (24, 100, 60, 8), (40, 24, 48, 10)):
+        wl = configs.tiny(nxy=nxy, nz=14, cols=cols, rows=rows, views_per_turn=72, turns=3, feed=24.0,
+                          dxy=2.0, slices_per_pitch=spp)
+        geom = wl.geom.as_dict()
+        plans.append(K.Plan(geom, wl.grid.as_dict(), device=0))
+        torch.manual_seed(rows)
+        gFs.append(K.filter_views(plans[-1], torch.rand(geom["n_views"], rows, cols, device="cuda")))
+    alone = [K.backproject(p, g) for p, g in zip(plans, gFs)]
+    for order in ((0, 1, 2, 3), (3, 2, 1, 0), (2, 1), (0, 2)):
+        for i, v in zip(order, K.backproject_batch([plans[i] for i in order], [gFs[i] for i in order])):
+            assert torch.equal(v, alone[i])
+    # a plan alone has few tasks and is split over teams; as many voxels as are not, over two shapes
+    big = []
+    for cols, rows, spp in ((160, 16, 24), (60, 32, 12)):
+        wl = configs.tiny(nxy=200, nz=48, cols=cols, rows=rows, views_per_turn=72, turns=4, feed=24.0, dxy=0.4,
+                          slices_per_pitch=spp)
+        geom = wl.geom.as_dict()
+        p = K.Plan(geom, wl.grid.as_dict(), device=0)
+        sino = torch.rand(geom["n_views"], rows, cols, device="cuda")
+        big.append((p, K.filter_views(p, sino)))
+    alone = [K.backproject(p, g) for p, g in big]
+    for v, a in zip(K.backproject_batch(*zip(*big)), alone):
+        assert torch.equal(v, a)
