@@ -252,8 +252,8 @@ int katsevich_backproject(katsevich_plan_t plan, const float *d_gF, float *d_vol
  * (katsevich_filter output of plans[i]) into d_vol[i], exactly as katsevich_backproject
  * would (bit-identical results).  One launch covers the (pitch, slice run, tile) tasks of
  * up to 16 items, so reconstructions of different sizes, pitches and grids fill the GPU
- * together; items whose footprint boxes take different LDS tiles, or whose size is split in
- * another way, are grouped apart (see bp_box_rows / bp_box_cols of katsevich_plan_info).  All plans
+ * together; items of many tasks whose footprint boxes take different LDS tiles, and items whose size
+ * is split in another way, are grouped apart (see bp_box_rows / bp_box_cols of katsevich_plan_info).  All plans
  * must be bound and use the same bp_slices.  No device memory besides the arrays named;
  * the host arrays may be reused when the call returns.  Asynchronous on stream.
  * Errors: KATS_EINVAL, KATS_ENOTBOUND, KATS_EHIP. */
