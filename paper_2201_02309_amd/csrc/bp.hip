@@ -485,9 +485,16 @@ static BpClass kernel_class(const KParams &k) {
     c.split = kWhole;
     if (k.bp_kz != 16) return c;
     const long long full = k.n_valid / ((long long)kT * kT * 16);
+    // Layers and workgroups that have slices.  A team workgroup fills a CU, so a thin volume, which has
+    // many workgroups for its voxels, keeps single ones, and whole ones where halves would be empty.
+    // Reconstruction whole / halves / halves in 4 teams, us: 356^2 x 5 (495 workgroups) 340 / 348 / 378,
+    // 300^2 x 10 (352) 374 / 340 / 377, 256^2 x 12 (256) 379 / 314 / 287
+    const long long last = k.nz - (long long)(k.n_pitches - 1) * k.ns;
+    const long long layers = (k.n_pitches - 1) * ((k.ns + 15ll) / 16) + (last + 15) / 16;
+    const bool many = k.n_valid / (kT * kT) * layers >= 300ll * k.nz;
     if (full < 80) c.split = kQuartersTeams;
-    else if (full < 220) c.split = kHalvesTeams;
-    else if (full < 450 && c.shape <= 1) c.split = kHalves;
+    else if (full < 220 && !many) c.split = kHalvesTeams;
+    else if (full < 450 && c.shape <= 1 && k.nz > 8 * layers) c.split = kHalves;
     // (the widest shape: 136 floats, 38 rows and more do not fit four times)
     if (kTeams[c.split] > 1 && c.shape < kFallback && bp_bytes(kTeams[c.split], kShapeCols[c.shape] + 8, k.bp_box_rows < 32 ? 32 : k.bp_box_rows, 0) + 64 > kLdsBytes)
         c.split = kHalves;

@@ -98,7 +98,7 @@ inline BpArgs bp_args(const KParams &k) {
 //
 // Blocks go to the eight XCDs in turn, each with an L2 of its own, so with neighbouring tiles side
 // by side in the grid every XCD reads the whole filtered window of every layer.  In layers of at least
-// `least` tiles the blocks of one XCD take a compact part instead: the tiles are numbered along bands
+// `least` tiles (kXcdForward, kXcdAdjoint) the blocks of one XCD take a compact part instead: the tiles are numbered along bands
 // of a quarter of the rows, column by column, each quarter of the numbering is cut into eight
 // segments, and XCD x takes segment x + z + quarter.  Parts differ in work (corners outside the field
 // of view) and an XCD cannot take work from another, hence four quarters a layer, and the turn from
@@ -106,11 +106,11 @@ inline BpArgs bp_args(const KParams &k) {
 // reconstruction 10.46 -> 10.08 ms, whole adjoint 42.5 -> 41.8 ms; 512 x 512 x 10 (network), forward and
 // adjoint 2.25 -> 1.90 ms.  Smaller layers read little, and their fewer blocks show what balance is
 // lost.  Plain order / this one by tiles, ms:
-//   forward   256: 4.52 / 4.48   361 (301^2 x 77): 3.00 / 3.04   400: 4.87 / 4.83   576: 3.80 / 3.74
+//   forward   529, one layer (356^2 x 5): 0.340 / 0.354   256: 4.52 / 4.48   361 (301^2 x 77): 3.00 / 3.04   400: 4.87 / 4.83   576: 3.80 / 3.74
 //             784: 4.90 / 4.75   1024 (512^2 x 32): 3.29 / 3.20
 //   adjoint   256 (sparse): 18.70 / 18.95   400: 14.74 / 14.70   576: 12.88 / 12.98   784: 16.41 / 16.57
 //             1024: 11.68 / 11.15
-constexpr unsigned kXcdForward = 512, kXcdAdjoint = 1024;      // least tiles
+constexpr unsigned kXcdForward = 768, kXcdAdjoint = 1024;      // least tiles
 struct TileAt {
     int x, y;
 };
