@@ -313,8 +313,9 @@ __global__ __launch_bounds__(kCT) void k_prelu_grad(PreluArgs a, double *__restr
     double sum = 0.0;
     const long long e0 = (long long)chunk * kPreluBlock, e1 = min(e0 + kPreluBlock, a.n);
     auto one = [&](float xv, float gv) {
+        // (no product where x > 0: an infinite cotangent times 0 would be a NaN)
         const bool on = xv > 0.0f;
-        sum = fma(on ? 0.0 : (double)xv, (double)gv, sum);
+        sum = on ? sum : fma((double)xv, (double)gv, sum);
         return on ? gv : w * gv;
     };
     if (VEC) {
