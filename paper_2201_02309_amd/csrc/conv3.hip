@@ -179,6 +179,12 @@ __global__ __launch_bounds__(kCT, 2) void k_conv3(Conv3Args a) {
 // tasks; a wave's sums are float32, the workgroup's four are added in LDS, the workgroups' in float64.
 // The bias gradient may cancel to nothing: it is summed in float64 throughout, its partials stored as
 // two floats.
+// Past the volume's edges dy is taken as 0, and so has to be the x it meets: the last row and column are
+// neighbours of such samples, and 0 times a value that is not finite is no 0.  RW, RH: the width, the
+// height is no multiple of the tile's.  A lane in the column past the edge then reads the zeros beside
+// its own, a row past it takes a select.  16 -> 16 channels, without / with, us: 586 x 16 x 627 (RW)
+// 839 / 848, 10 x 300 x 300 (both) 157.6 / 160.4; 10 x 512 x 512, which needs neither, 387.
+template <bool RH, bool RW>
 __global__ __launch_bounds__(kCT, 2) void k_conv3_wgrad(Conv3Args a, const float *__restrict__ dy,
                                                         float *__restrict__ part) {
     constexpr int CH = 16, CS = 388;
@@ -211,12 +217,14 @@ __global__ __launch_bounds__(kCT, 2) void k_conv3_wgrad(Conv3Args a, const float
 #pragma unroll 1
             for (int half = 0; half < 2; ++half) {
                 const int col = 16 * half + 4 * wave + k4;
+                const bool win = w0 + col < a.W;
+                const int left = !RW || win ? 0 : 1;
                 float gy[kTH];
 #pragma unroll
                 for (int r = 0; r < kTH; ++r) {
                     const int h = h0 + r, w = w0 + col;
                     gy[r] = 0.0f;
-                    if (h < a.H && n16 < a.cout && w < a.W) gy[r] = (g + z * a.yd + (long long)h * a.W)[(unsigned)n16 * (unsigned)a.yc + (unsigned)w];
+                    if (h < a.H && n16 < a.cout && win) gy[r] = (g + z * a.yd + (long long)h * a.W)[(unsigned)n16 * (unsigned)a.yc + (unsigned)w];
                     db += gy[r];
                 }
 #pragma unroll
@@ -226,13 +234,15 @@ __global__ __launch_bounds__(kCT, 2) void k_conv3_wgrad(Conv3Args a, const float
                     for (int kw = 0; kw < 3; ++kw) {
                         float b[kPH];
 #pragma unroll
-                        for (int r = 0; r < kPH; ++r) b[r] = L[r * kPW + kw];
+                        for (int r = 0; r < kPH; ++r) b[r] = L[r * kPW + (kw ? kw : left)];
 #pragma unroll
                         for (int r = 0; r < kTH; ++r)
 #pragma unroll
-                            for (int kh = 0; kh < 3; ++kh)
+                            for (int kh = 0; kh < 3; ++kh) {
+                                const float xv = RH && kh == 0 && r > 0 ? (h0 + r < a.H ? b[r] : 0.0f) : b[r + kh];
                                 acc[9 * kd + 3 * kh + kw] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                    gy[r], b[r + kh], acc[9 * kd + 3 * kh + kw], 0, 0, 0);
+                                    gy[r], xv, acc[9 * kd + 3 * kh + kw], 0, 0, 0);
+                            }
                     }
                 }
             }
@@ -411,7 +421,9 @@ hipError_t launch_conv3_wgrad(Conv3Args a, const float *dy, float *dw, float *db
     split(a);
     const long long tasks = (long long)a.tiles_w * a.tiles_h * a.nseg * a.B;
     const int blocks = (int)(tasks < kConv3Blocks ? tasks : kConv3Blocks);
-    hipLaunchKernelGGL(k_conv3_wgrad, dim3(blocks), dim3(kCT), 0, s, a, dy, part);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kCT), 0, s, a, dy, part); };
+    if (a.H % kTH) a.W % kTW ? go(k_conv3_wgrad<true, true>) : go(k_conv3_wgrad<true, false>);
+    else a.W % kTW ? go(k_conv3_wgrad<false, true>) : go(k_conv3_wgrad<false, false>);
     hipLaunchKernelGGL(k_conv3_wsum, dim3(27 * 16 + 1), dim3(kCT), 0, s, (const float *)part, blocks, a.cin,
                        a.cout, dw, db);
     return hipGetLastError();
