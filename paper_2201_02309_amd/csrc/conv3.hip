@@ -177,8 +177,8 @@ __global__ __launch_bounds__(kCT, 2) void k_conv3(Conv3Args a) {
 // from the LDS planes (a row's samples serve three taps).  CS = 4 (mod 64): a wave reads 16
 // channels x 4 columns from different banks.  Workgroups are persistent over (tile, depth range)
 // tasks; a wave's sums are float32, the workgroup's four are added in LDS, the workgroups' in float64.
-// The bias gradient may cancel to nothing: it is summed in float64 throughout, its partials stored as
-// two floats.
+// The bias gradient may cancel to nothing: it is summed in float64 throughout, its partials stored
+// whole, as the words of a double (a float and its remainder would turn an infinity into a NaN).
 // Past the volume's edges dy is taken as 0, and so has to be the x it meets: the last row and column are
 // neighbours of such samples, and 0 times a value that is not finite is no 0.  RW, RH: the width, the
 // height is no multiple of the tile's.  A lane in the column past the edge then reads the zeros beside
@@ -272,9 +272,8 @@ __global__ __launch_bounds__(kCT, 2) void k_conv3_wgrad(Conv3Args a, const float
             }
         if (lane < 16) {
             dbs[lane] = w ? dbs[lane] + db : db;
-            const float hi = (float)dbs[lane];
-            lds[27 * 256 + lane] = hi;
-            lds[27 * 256 + 16 + lane] = (float)(dbs[lane] - (double)hi);
+            lds[27 * 256 + lane] = __int_as_float(__double2hiint(dbs[lane]));
+            lds[27 * 256 + 16 + lane] = __int_as_float(__double2loint(dbs[lane]));
         }
     }
     __syncthreads();
@@ -289,10 +288,15 @@ __global__ __launch_bounds__(kCT) void k_conv3_wsum(const float *__restrict__ pa
     const int j = threadIdx.x & 15, g = threadIdx.x >> 4;
     const int e = blockIdx.x * 16 + j;
     double s = 0.0;
+    if (e < 27 * 256) {
 #pragma unroll 8
-    for (int p = g; p < np; p += 16) s += (double)part[(size_t)p * kConv3Part + e];
-    if (e >= 27 * 256)
-        for (int p = g; p < np; p += 16) s += (double)part[(size_t)p * kConv3Part + e + 16];
+        for (int p = g; p < np; p += 16) s += (double)part[(size_t)p * kConv3Part + e];
+    } else {
+        for (int p = g; p < np; p += 16) {
+            const float *h = part + (size_t)p * kConv3Part + e;
+            s += __hiloint2double(__float_as_int(h[0]), __float_as_int(h[16]));
+        }
+    }
     sh[g][j] = s;
     __syncthreads();
     if (g != 0) return;

@@ -66,3 +66,18 @@ def test_weight_gradient_at_the_edges(H, W, bad):
                     want[:, :, d, h, w] = (gs[:, None] * xs[None]).sum(dim=(2, 3, 4))
         print(f"[case] {H} x {W}, {bad} at {at}: {int((~torch.isfinite(want)).sum())} of 162", flush=True)
         _same(got, want)
+
+
+# cotangents whose sums are infinite, not numbers, and pass float32's range on the way to one in it
+@pytest.mark.parametrize("values", [(INF,), (-INF, 5.0), (INF, -INF), (NAN,), (3.0e38, 3.0e38, -3.0e38),
+                                    (3.0e38, 3.0e38)])
+def test_bias_gradient(values):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    m = N.Conv3x3x3(2, 3).cuda()
+    x = torch.ones(1, 2, 3, 9, 33, device="cuda")
+    g = torch.zeros(1, 3, 3, 9, 33)
+    for i, v in enumerate(values):
+        g[0, 1, 1, 4, 3 + 7 * i] = v
+    got = torch.autograd.grad(m(x), m.bias, g.cuda())[0]
+    _same(got, g.double().sum(dim=(0, 2, 3, 4)).float())
