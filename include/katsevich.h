@@ -326,8 +326,9 @@ int katsevich_rmse_ssim_noscratch(const float *d_f, const float *d_ref, uint64_t
 /* ---- 3 x 3 x 3 convolutions of the dual-domain network (Sec. III-A) on the float32 matrix cores.
  * Plan-free, asynchronous on stream, no device allocation.  shape: batch, input channels, output
  * channels (at most 16 each), depth, height, width (host array of 6); strides: of batch, channel and
- * depth in floats (host arrays of 3; rows contiguous, planes of height x width).  Errors:
- * KATS_EINVAL, KATS_EWORKSPACE, KATS_EHIP. */
+ * depth in floats (host arrays of 3; rows contiguous, planes of height x width).  In katsevich_conv3 and
+ * katsevich_conv3_grad the channels of one depth lie within 2^30 floats: (channels - 1) times their
+ * stride + height x width is at most that.  Errors: KATS_EINVAL, KATS_EWORKSPACE, KATS_EHIP. */
 
 /* y = bias + zero-padded (1 voxel) correlation of x with the weights w [out][in][3][3][3]; bias
  * may be null.  transposed: w is [in][out][3][3][3] read flipped, which is the gradient of that

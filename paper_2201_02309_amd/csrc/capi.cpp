@@ -574,11 +574,13 @@ static int conv3_args(const char *who, const float *x, const int64_t *xs, const 
     // grid limits of the launches (65535 in y and z, tiles in x)
     if (shape[0] > 65535 || shape[3] > 4 * 65535 || ((shape[4] + 7) / 8) * ((shape[5] + 31) / 32) > INT32_MAX / shape[0])
         return fail(KATS_EINVAL, std::string(who) + ": volume too large");
-    // a lane's offset within a depth is 32 bits
-    const int64_t plane = shape[4] * shape[5];
-    for (const int64_t c : {xs[1], ys[1]})
-        if (c < 0 || 16 * c + plane > (int64_t)1 << 30)
-            return fail(KATS_EINVAL, std::string(who) + ": channel stride negative or too large");
+    // a lane's offset within a depth is 32 bits (the stride of a single channel plays no part)
+    const int64_t most = (int64_t)1 << 30;
+    if (shape[4] * shape[5] > most) return fail(KATS_EINVAL, std::string(who) + ": volume too large");
+    const int64_t xc = shape[1] > 1 ? xs[1] : 0, yc = shape[2] > 1 ? ys[1] : 0;
+    if (xc < 0 || yc < 0 || xc > most || yc > most || (shape[1] - 1) * xc > most - shape[4] * shape[5] ||
+        (shape[2] - 1) * yc > most - shape[4] * shape[5])
+        return fail(KATS_EINVAL, std::string(who) + ": channel stride negative or too large");
     a.x = x;
     a.B = (int)shape[0];
     a.cin = (int)shape[1];
@@ -587,10 +589,10 @@ static int conv3_args(const char *who, const float *x, const int64_t *xs, const 
     a.H = (int)shape[4];
     a.W = (int)shape[5];
     a.xb = xs[0];
-    a.xc = xs[1];
+    a.xc = xc;
     a.xd = xs[2];
     a.yb = ys[0];
-    a.yc = ys[1];
+    a.yc = yc;
     a.yd = ys[2];
     return KATS_OK;
 }

@@ -529,10 +529,18 @@ def rows_dense(t):
     return (W == 1 or t.stride(-1) == 1) and (H == 1 or t.stride(-2) == W)
 
 
+def dense_volume(t):
+    """t itself where katsevich_conv3 and katsevich_conv3_grad take its strides (planes stored densely,
+    channels at most 2^30 floats apart), otherwise a dense copy of it."""
+    H, W = t.shape[-2:]
+    near = (t.shape[1] - 1) * t.stride(1) + H * W <= 1 << 30
+    return t if near and rows_dense(t) else t.contiguous()
+
+
 def conv3(x, w, bias=None, transposed=False):
     """katsevich_conv3: 3x3x3 convolution (zero padding 1) of x [B, cin, D, H, W] with w [cout, cin,
     3, 3, 3], or with `transposed` its gradient with respect to the input, w [cin, cout, 3, 3, 3].
-    The result is stored as [B, D, cout, H, W].  x: float32, planes dense."""
+    The result is stored as [B, D, cout, H, W].  x: float32, strides as of dense_volume."""
     import torch
     B, cin, D, H, W = x.shape
     cout = w.shape[1 if transposed else 0]

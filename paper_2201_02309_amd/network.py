@@ -101,11 +101,11 @@ class _Conv3Fn(torch.autograd.Function):
                 grads = iter(torch.autograd.grad(_conv3x3x3(*args), [t for t, n in zip(args, want) if n],
                                                  gy, create_graph=again))
             return tuple(next(grads) if n else None for n in want)
-        gy = gy if _K.rows_dense(gy) else gy.contiguous()
+        gy = _K.dense_volume(gy)
         gx = _K.conv3(gy, weight.contiguous(), transposed=True) if want[0] else None
         gw = gb = None
         if want[1] or want[2]:
-            gw, gb = _K.conv3_grad(x if _K.rows_dense(x) else x.contiguous(), gy, tuple(weight.shape))
+            gw, gb = _K.conv3_grad(_K.dense_volume(x), gy, tuple(weight.shape))
         return gx, gw if want[1] else None, gb if want[2] else None
 
 
@@ -129,7 +129,7 @@ class Conv3x3x3(nn.Module):
             return _conv3x3x3(x, w, b)
         if torch.is_grad_enabled() and (x.requires_grad or w.requires_grad or b.requires_grad):
             return _Conv3Fn.apply(x.clone() if self.copy_input and w.requires_grad else x, w.clone(), b)
-        return _K.conv3(x if _K.rows_dense(x) else x.contiguous(), w.contiguous(), b.contiguous())
+        return _K.conv3(_K.dense_volume(x), w.contiguous(), b.contiguous())
 
 
 class _PReLUFn(torch.autograd.Function):

@@ -1,0 +1,38 @@
+"""Host checks of the network kernels' entry points: which shapes and strides they take.  Without a GPU
+an accepted call ends at its launch (KATS_EHIP); the buffers are never touched."""
+from ctypes import c_int64, c_uint64, c_void_p
+
+import pytest
+
+torch = pytest.importorskip("torch")
+K = pytest.importorskip("paper_2201_02309_amd")
+from paper_2201_02309_amd import network as N  # noqa: E402
+
+EINVAL, EHIP = -1, -6
+PTR = c_void_p(1 << 20)
+
+pytestmark = pytest.mark.skipif(torch.cuda.is_available(), reason="accepted calls would launch")
+
+
+def _conv(shape, xs, ys):
+    lib = K.load_library()
+    a = ((c_int64 * 3)(*xs), (c_int64 * 3)(*ys), (c_int64 * 6)(*shape))
+    st = {lib.katsevich_conv3(PTR, a[0], PTR, None, PTR, a[1], a[2], 0, None),
+          lib.katsevich_conv3_grad(PTR, a[0], PTR, a[1], a[2], PTR, PTR, PTR,
+                                   c_uint64(lib.katsevich_conv3_scratch_bytes()), None)}
+    assert len(st) == 1
+    return st.pop()
+
+
+PLANE = 512 * 512
+
+
+@pytest.mark.parametrize("cin,xc,ok", [
+    (1, 300 * PLANE, True), (1, 1 << 62, True),              # one channel: its stride plays no part
+    (16, 272 * PLANE, True), (16, (4096 - 1) * PLANE // 15, True), (16, 274 * PLANE, False),
+    (2, (1 << 30) - PLANE, True), (2, (1 << 30) - PLANE + 1, False), (2, 1 << 62, False), (2, -1, False)])
+def test_channel_strides(cin, xc, ok):
+    want = EHIP if ok else EINVAL
+    dense = (16 * PLANE, PLANE, 16 * PLANE)
+    assert _conv((1, cin, 16, 10, 512, 512), (16 * xc if xc < 1 << 40 else xc, xc, PLANE), dense) == want
+    assert _conv((1, 16, cin, 10, 512, 512), dense, (0, xc, PLANE)) == want

@@ -1,0 +1,44 @@
+"""Ways in which programs call the network's layers: volumes that are parts of larger ones, scripted,
+compiled and traced networks, frozen layers, function modes."""
+import pytest
+
+torch = pytest.importorskip("torch")
+N = pytest.importorskip("paper_2201_02309_amd.network")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.manual_seed(0)
+
+
+# a depth slice of a large volume: one channel, and channels too far apart for 32-bit offsets
+@pytest.mark.parametrize("cin,cout,depth", [(1, 4, 300), (16, 4, 300), (4, 16, 1100)])
+def test_depth_slices(cin, cout, depth):
+    m = N.Conv3x3x3(cin, cout).cuda()
+    big = torch.empty(1, cin, depth, 512, 512, device="cuda")
+    x = big[:, :, 7:10].normal_()
+    dense = x.clone(memory_format=torch.contiguous_format)
+    with torch.no_grad():
+        assert torch.equal(m(x), m(dense))
+    x, dense = x.detach().requires_grad_(), dense.requires_grad_()
+    y = m(x)
+    assert type(y.grad_fn).__name__ == "_Conv3FnBackward"
+    far = torch.empty(1, cout, depth, 512, 512, device="cuda")[:, :, 5:8].normal_()
+    ref = torch.autograd.grad(m(dense), (dense, m.weight, m.bias), far.clone(memory_format=torch.contiguous_format))
+    for a, b in zip(torch.autograd.grad(y, (x, m.weight, m.bias), far), ref):
+        assert torch.equal(a, b)
+
+
+def test_network_on_a_slab():
+    net = N.SubNet(4, 2).cuda()
+    vol = torch.randn(512, 512, 512, device="cuda")
+    slab = vol[None, None, 100:104]
+    with torch.no_grad():
+        ref = net(slab.clone())
+        assert torch.equal(net(slab), ref)
+    net(slab).sum().backward()
+    assert all(bool(torch.isfinite(p.grad).all()) for p in net.parameters())
