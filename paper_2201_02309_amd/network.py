@@ -33,10 +33,10 @@ def _conv3x3x3(x, weight, bias):
     return _conv_stack(stack, D, weight, bias)
 
 
-def _conv_stack(stack, D, weight, bias):
+def _conv_stack(stack, D: int, weight, bias):
     """The 2-D convolution of [B D, 3 C, H, W] depth-shifted copies -> [B, cout, D, H, W]."""
-    (BD, C3, H, W), cout = stack.shape, weight.shape[0]
-    B, C = BD // D, C3 // 3
+    BD, C3, H, W = stack.shape
+    B, C, cout = BD // D, C3 // 3, weight.shape[0]
     w2 = weight.permute(0, 2, 1, 3, 4).reshape(cout, 3 * C, 3, 3)
     y = F.conv2d(stack, w2, bias, padding=1)
     return y.reshape(B, D, cout, H, W).permute(0, 2, 1, 3, 4)
@@ -50,7 +50,7 @@ def _plain(*tensors):
         if type(t) not in (torch.Tensor, nn.Parameter) or t.dtype != torch.float32 or not t.is_cuda \
                 or t.device != tensors[0].device or not torch._C._has_storage(t):
             return False
-    return not (torch.is_autocast_enabled("cuda") or torch.jit.is_tracing() or torch.jit.is_scripting()
+    return not (torch.is_autocast_enabled("cuda") or torch.jit.is_tracing()
                 or torch.compiler.is_compiling() or torch.autograd.forward_ad._current_level >= 0
                 or torch._C._functorch.peek_interpreter_stack() is not None
                 or torch._C._len_torch_dispatch_stack() > 0)
@@ -124,6 +124,12 @@ class Conv3x3x3(nn.Module):
         self.bias = nn.Parameter(ref.bias.detach().clone())
 
     def forward(self, x):                                   # x [B, C, D, H, W]
+        if torch.jit.is_scripting():                        # (a script compiles this branch alone)
+            return _conv3x3x3(x, self.weight, self.bias)
+        else:
+            return self._eager(x)
+
+    def _eager(self, x):
         w, b = self.weight, self.bias
         if not _native_conv(x, w, b):
             return _conv3x3x3(x, w, b)
@@ -161,11 +167,17 @@ class PReLU(nn.PReLU):
     """nn.PReLU whose gradients on float32 volumes of one GPU run on the library's kernel."""
 
     def forward(self, x):
+        if torch.jit.is_scripting():                        # (as in Conv3x3x3)
+            return F.prelu(x, self.weight)
+        else:
+            return self._eager(x)
+
+    def _eager(self, x):
         w = self.weight
         if torch.is_grad_enabled() and (x.requires_grad or w.requires_grad) and _plain(x, w) \
                 and _native_volume(x, w.numel()):
             return _PReLUFn.apply(x, w)
-        return super().forward(x)
+        return F.prelu(x, w)
 
 
 class SubNet(nn.Module):

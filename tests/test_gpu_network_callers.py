@@ -42,3 +42,12 @@ def test_network_on_a_slab():
         assert torch.equal(net(slab), ref)
     net(slab).sum().backward()
     assert all(bool(torch.isfinite(p.grad).all()) for p in net.parameters())
+
+
+def test_script():
+    net = N.SubNet(4, 2).cuda()
+    x = torch.randn(1, 1, 3, 20, 33, device="cuda", requires_grad=True)
+    y = torch.jit.script(net)(x)
+    assert torch.equal(y, net(x))
+    y.sum().backward()
+    assert bool(torch.isfinite(x.grad).all())

@@ -1,0 +1,26 @@
+"""The network under torch's scripting and tracing tools, and on empty volumes, on the CPU: what torch's
+own operators take."""
+import pytest
+
+torch = pytest.importorskip("torch")
+N = pytest.importorskip("paper_2201_02309_amd.network")
+
+
+@pytest.fixture
+def net():
+    torch.manual_seed(2)
+    return N.SubNet(channels=4, blocks=2)
+
+
+X = (1, 1, 3, 5, 6)
+
+
+def test_script(net):
+    x = torch.randn(X)
+    s = torch.jit.script(net)
+    for shape in (X, (2, 1, 1, 7, 4)):
+        v = torch.randn(shape)
+        assert torch.equal(s(v), net(v))
+    for a, b in zip(torch.autograd.grad(s(x).square().sum(), tuple(s.parameters())),
+                    torch.autograd.grad(net(x).square().sum(), tuple(net.parameters()))):
+        assert torch.allclose(a, b, rtol=1e-5, atol=1e-5)
