@@ -46,12 +46,14 @@ def _plain(*tensors):
     """Whether every tensor is a plain float32 one of the same GPU, and no autocast, tracing,
     compilation, forward-mode derivative, function transform or dispatch mode is at work, which
     need torch's operators."""
+    if torch.compiler.is_compiling():          # first: a compiler follows what comes after it
+        return False
     for t in tensors:
         if type(t) not in (torch.Tensor, nn.Parameter) or t.dtype != torch.float32 or not t.is_cuda \
                 or t.device != tensors[0].device or not torch._C._has_storage(t):
             return False
     return not (torch.is_autocast_enabled("cuda") or torch.jit.is_tracing()
-                or torch.compiler.is_compiling() or torch.autograd.forward_ad._current_level >= 0
+                or torch.autograd.forward_ad._current_level >= 0
                 or torch._C._functorch.peek_interpreter_stack() is not None
                 or torch._C._len_torch_dispatch_stack() > 0)
 

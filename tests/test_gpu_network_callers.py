@@ -51,3 +51,22 @@ def test_script():
     assert torch.equal(y, net(x))
     y.sum().backward()
     assert bool(torch.isfinite(x.grad).all())
+
+
+def test_compile_and_export():
+    """Whole graphs, of torch's operators alone."""
+    net = N.SubNet(4, 2).cuda()
+    x = torch.randn(1, 1, 3, 20, 33, device="cuda")
+    want = N.SubNet.forward(net, x)
+    gw = torch.autograd.grad(want.sum(), net.out.weight)[0]
+    torch._dynamo.reset()
+    y = torch.compile(net, backend="eager", fullgraph=True)(x)
+    assert torch.equal(y, want)
+    assert torch.allclose(torch.autograd.grad(y.sum(), net.out.weight)[0], gw, rtol=1e-4, atol=1e-3 * float(gw.abs().max()))
+    with torch.no_grad():
+        torch._dynamo.reset()
+        y = torch.compile(net, backend="eager", fullgraph=True)(x)
+        assert torch.allclose(y, want, rtol=1e-5, atol=1e-5)
+        for strict in (False, True):
+            y = torch.export.export(net, (x,), strict=strict).module()(x)
+            assert torch.allclose(y, want, rtol=1e-5, atol=1e-5)
