@@ -70,7 +70,7 @@ def _native_volume(x, channels):
 
 def _native_conv(x, weight, bias):
     """Whether the library's kernels take this convolution (at most 16 channels on either side)."""
-    if x.dim() != 5 or not _plain(x, weight, bias):
+    if not _plain(x, weight, bias) or x.dim() != 5:     # (a symbolic x has no dim() to compare)
         return False
     cin, cout = x.shape[1], weight.shape[0]
     return (1 <= cout <= 16 and cin <= 16 and tuple(weight.shape) == (cout, cin, 3, 3, 3)
@@ -176,7 +176,7 @@ class PReLU(nn.PReLU):
 
     def _eager(self, x):
         w = self.weight
-        if torch.is_grad_enabled() and (x.requires_grad or w.requires_grad) and _plain(x, w) \
+        if torch.is_grad_enabled() and _plain(x, w) and (x.requires_grad or w.requires_grad) \
                 and _native_volume(x, w.numel()):
             return _PReLUFn.apply(x, w)
         return F.prelu(x, w)

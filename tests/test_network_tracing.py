@@ -24,3 +24,11 @@ def test_script(net):
     for a, b in zip(torch.autograd.grad(s(x).square().sum(), tuple(s.parameters())),
                     torch.autograd.grad(net(x).square().sum(), tuple(net.parameters()))):
         assert torch.allclose(a, b, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("grad", [True, False])
+def test_symbolic_trace(net, grad):
+    x = torch.randn(X)
+    with torch.set_grad_enabled(grad):
+        traced = torch.fx.symbolic_trace(net)
+        assert torch.equal(traced(x), net(x))
