@@ -30,14 +30,14 @@ def _conv3x3x3(x, weight, bias):
     xp = F.pad(x, (0, 0, 0, 0, 1, 1))
     stack = torch.cat([xp[:, :, k:k + D] for k in range(3)], dim=1)      # [B, 3C, D, H, W]
     stack = stack.permute(0, 2, 1, 3, 4).reshape(B * D, 3 * C, H, W)
-    return _conv_stack(stack, D, weight, bias)
+    return _conv_stack(stack, B, D, weight, bias)
 
 
-def _conv_stack(stack, D: int, weight, bias):
+def _conv_stack(stack, B: int, D: int, weight, bias):
     """The 2-D convolution of [B D, 3 C, H, W] depth-shifted copies -> [B, cout, D, H, W]."""
-    BD, C3, H, W = stack.shape
-    B, C, cout = BD // D, C3 // 3, weight.shape[0]
-    w2 = weight.permute(0, 2, 1, 3, 4).reshape(cout, 3 * C, 3, 3)
+    _, C3, H, W = stack.shape
+    cout = weight.shape[0]
+    w2 = weight.permute(0, 2, 1, 3, 4).reshape(cout, C3, 3, 3)
     y = F.conv2d(stack, w2, bias, padding=1)
     return y.reshape(B, D, cout, H, W).permute(0, 2, 1, 3, 4)
 
@@ -88,7 +88,7 @@ class _Conv3Fn(torch.autograd.Function):
     def forward(ctx, x, weight, bias):
         ctx.save_for_backward(x, weight)
         stack = _K.stack3(x if _K.rows_dense(x) else x.contiguous())
-        return _conv_stack(stack, x.shape[2], weight, bias)
+        return _conv_stack(stack, x.shape[0], x.shape[2], weight, bias)
 
     @staticmethod
     def backward(ctx, gy):

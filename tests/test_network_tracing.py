@@ -32,3 +32,12 @@ def test_symbolic_trace(net, grad):
     with torch.set_grad_enabled(grad):
         traced = torch.fx.symbolic_trace(net)
         assert torch.equal(traced(x), net(x))
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 0, 5, 6), (0, 1, 3, 5, 6)])
+def test_empty_volumes(net, shape):
+    x = torch.randn(shape, requires_grad=True)
+    y = net(x)
+    assert y.shape == shape
+    y.sum().backward()
+    assert x.grad.shape == shape and all(bool((p.grad == 0).all()) for p in net.parameters())
