@@ -86,13 +86,17 @@ class _Conv3Fn(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, x, weight, bias):
-        ctx.save_for_backward(x, weight)
+        # (x plays a part in the weight's gradient alone: a frozen layer's may change)
+        ctx.save_for_backward(x if ctx.needs_input_grad[1] else None, weight)
+        ctx.shape = x.shape
         stack = _K.stack3(x if _K.rows_dense(x) else x.contiguous())
         return _conv_stack(stack, x.shape[0], x.shape[2], weight, bias)
 
     @staticmethod
     def backward(ctx, gy):
         x, weight = ctx.saved_tensors
+        if x is None:
+            x = weight.new_zeros(1, 1, 1, *ctx.shape[3:]).expand(ctx.shape)
         want = ctx.needs_input_grad
         again = torch.is_grad_enabled()
         if again or not _native_conv(gy, weight.transpose(0, 1), x.new_empty(x.shape[1])):

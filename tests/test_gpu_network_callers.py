@@ -70,3 +70,29 @@ def test_compile_and_export():
         for strict in (False, True):
             y = torch.export.export(net, (x,), strict=strict).module()(x)
             assert torch.allclose(y, want, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("weight,bias,shape", [(False, False, (1, 3, 4, 9, 33)), (False, True, (2, 3, 4, 9, 33)),
+                                               (True, False, (1, 3, 4, 9, 33))])
+def test_frozen_layers(weight, bias, shape):
+    """The input changes in place between the forward and the backward; first and second derivatives."""
+    m = N.Conv3x3x3(3, 5).cuda()
+    m.weight.requires_grad_(weight)
+    m.bias.requires_grad_(bias)
+    x = torch.randn(shape, device="cuda", requires_grad=True)
+    wanted = [x] + [p for p in m.parameters() if p.requires_grad]
+    for again in (False, True):
+        def grads(f):
+            h = x * 2
+            y = f(h)
+            with torch.no_grad():
+                h.add_(1)
+            g = torch.autograd.grad(y, wanted, torch.cos(y.detach()), create_graph=again)
+            if again:
+                v = torch.ones(shape, device="cuda", requires_grad=True)
+                g = torch.autograd.grad((f(v * x) ** 2).sum(), x, create_graph=True)
+                g = torch.autograd.grad(g[0].square().sum(), [x, v])
+            return g
+        got = grads(m)
+        for a, b in zip(got, grads(lambda h: N._conv3x3x3(h, m.weight, m.bias))):
+            assert torch.allclose(a, b, rtol=1e-4, atol=1e-4 * float(b.abs().max()))
