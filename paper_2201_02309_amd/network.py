@@ -77,6 +77,16 @@ def _native_conv(x, weight, bias):
             and tuple(bias.shape) == (cout,) and _native_volume(x, cin))
 
 
+def _check_kept(gy, *kept):
+    """Hooks on saved tensors may hand back others than were kept, which torch's operators refuse and
+    the kernels would read out of range: every (tensor, shape) must have that shape and gy's type and
+    device."""
+    for t, shape in kept:
+        if t.dtype != gy.dtype or t.device != gy.device or t.shape != torch.Size(shape):
+            raise RuntimeError(f"a saved tensor came back as {t.dtype} {tuple(t.shape)} on {t.device}: "
+                               f"{gy.dtype} {tuple(shape)} on {gy.device} was kept")
+
+
 class _Conv3Fn(torch.autograd.Function):
     """_conv3x3x3 with its gradients on the library's kernels; a derivative that is itself to be
     differentiated, or whose gradient the kernels do not take, goes through _conv3x3x3 again.  x and
@@ -99,7 +109,8 @@ class _Conv3Fn(torch.autograd.Function):
             x = weight.new_zeros(1, 1, 1, *ctx.shape[3:]).expand(ctx.shape)
         want = ctx.needs_input_grad
         again = torch.is_grad_enabled()
-        if again or not _native_conv(gy, weight.transpose(0, 1), x.new_empty(x.shape[1])):
+        _check_kept(gy, (x, ctx.shape), (weight, (gy.shape[1], ctx.shape[1], 3, 3, 3)))
+        if again or not _plain(x, weight) or not _native_conv(gy, weight.transpose(0, 1), x.new_empty(x.shape[1])):
             with torch.enable_grad():
                 bias = weight.new_zeros(weight.shape[0], requires_grad=True)   # its value plays no part
                 args = [t if t.requires_grad else t.detach().requires_grad_(n)
@@ -158,6 +169,7 @@ class _PReLUFn(torch.autograd.Function):
         x, weight = ctx.saved_tensors
         want = ctx.needs_input_grad
         again = torch.is_grad_enabled()
+        _check_kept(gy, (x, gy.shape), (weight, gy.shape[1:2]))
         if again or not _plain(gy, x, weight):
             with torch.enable_grad():
                 args = [t if t.requires_grad else t.detach().requires_grad_(n) for t, n in zip((x, weight), want)]

@@ -96,3 +96,21 @@ def test_frozen_layers(weight, bias, shape):
         got = grads(m)
         for a, b in zip(got, grads(lambda h: N._conv3x3x3(h, m.weight, m.bias))):
             assert torch.allclose(a, b, rtol=1e-4, atol=1e-4 * float(b.abs().max()))
+
+
+@pytest.mark.parametrize("unpack", [lambda t: t.double(), lambda t: t.half(), lambda t: t.cpu(), lambda t: t[..., :1]])
+@pytest.mark.parametrize("layer", ["conv", "prelu"])
+def test_saved_tensors_handed_back_otherwise(layer, unpack):
+    """Hooks that hand back others than the saved tensors are refused, as torch's operators do."""
+    m = N.Conv3x3x3(3, 3).cuda() if layer == "conv" else N.PReLU(3).cuda()
+    x = torch.randn(1, 3, 4, 9, 33, device="cuda", requires_grad=True)
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, unpack):
+        y = m(x)
+    assert type(y.grad_fn).__name__ in ("_Conv3FnBackward", "_PReLUFnBackward")
+    with pytest.raises(RuntimeError):
+        y.sum().backward()
+    # and as they were, from the host's memory
+    with torch.autograd.graph.save_on_cpu():
+        y = m(x)
+    for a, b in zip(torch.autograd.grad(y.sum(), (x, m.weight)), torch.autograd.grad(m(x).sum(), (x, m.weight))):
+        assert torch.equal(a, b)
