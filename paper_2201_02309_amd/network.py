@@ -18,6 +18,8 @@ import math
 import torch
 import torch.nn.functional as F
 from torch import nn
+from torch.overrides import _get_current_function_mode_stack
+from torch.utils._device import DeviceContext
 
 from . import katsevich as _K
 from .katsevich import KatsevichFn, Plan
@@ -44,8 +46,8 @@ def _conv_stack(stack, B: int, D: int, weight, bias):
 
 def _plain(*tensors):
     """Whether every tensor is a plain float32 one of the same GPU, and no autocast, tracing,
-    compilation, forward-mode derivative, function transform or dispatch mode is at work, which
-    need torch's operators."""
+    compilation, forward-mode derivative, function transform, function or dispatch mode (other than
+    a default device) is at work, which need torch's operators."""
     if torch.compiler.is_compiling():          # first: a compiler follows what comes after it
         return False
     for t in tensors:
@@ -55,7 +57,8 @@ def _plain(*tensors):
     return not (torch.is_autocast_enabled("cuda") or torch.jit.is_tracing()
                 or torch.autograd.forward_ad._current_level >= 0
                 or torch._C._functorch.peek_interpreter_stack() is not None
-                or torch._C._len_torch_dispatch_stack() > 0)
+                or torch._C._len_torch_dispatch_stack() > 0
+                or any(not isinstance(m, DeviceContext) for m in _get_current_function_mode_stack()))
 
 
 def _native_volume(x, channels):

@@ -114,3 +114,27 @@ def test_saved_tensors_handed_back_otherwise(layer, unpack):
         y = m(x)
     for a, b in zip(torch.autograd.grad(y.sum(), (x, m.weight)), torch.autograd.grad(m(x).sum(), (x, m.weight))):
         assert torch.equal(a, b)
+
+
+def test_function_modes():
+    """A mode that takes torch's functions sees the layers' own; a default device changes nothing."""
+    class Seen(torch.overrides.TorchFunctionMode):
+        def __init__(self):
+            super().__init__()
+            self.names = []
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.names.append(getattr(func, "__name__", ""))
+            return func(*args, **(kwargs or {}))
+    m = torch.nn.Sequential(N.Conv3x3x3(3, 5), N.PReLU(5)).cuda()
+    x = torch.randn(1, 3, 4, 9, 33, device="cuda")
+    for grad in (False, True):
+        with torch.set_grad_enabled(grad):
+            with Seen() as seen:
+                y = m(x)
+            assert "conv2d" in seen.names and "prelu" in seen.names
+            assert torch.allclose(y, m(x), rtol=1e-5, atol=1e-5)
+    assert type(y.grad_fn).__name__ == "PreluKernelBackward0"
+    with torch.device("cuda"):
+        y = m(x)
+    assert type(y.grad_fn).__name__ == "_PReLUFnBackward"
