@@ -326,7 +326,10 @@ int katsevich_rmse_ssim_noscratch(const float *d_f, const float *d_ref, uint64_t
 /* ---- 3 x 3 x 3 convolutions of the dual-domain network (Sec. III-A) on the float32 matrix cores.
  * Plan-free, asynchronous on stream, no device allocation.  shape: batch, input channels, output
  * channels (at most 16 each), depth, height, width (host array of 6); strides: of batch, channel and
- * depth in floats (host arrays of 3; rows contiguous, planes of height x width).  In katsevich_conv3 and
+ * depth in floats (host arrays of 3; rows contiguous, planes of height x width).  Volumes are limited by
+ * their launches (KATS_EINVAL): less than 2^24 tiles of 8 x 32 samples a plane, a batch of 65535 and
+ * 262140 depths for the convolutions, 2^24 planes for katsevich_stack3 and 2^24 blocks of 8192 samples,
+ * each of one plane, for katsevich_prelu_grad.  In katsevich_conv3 and
  * katsevich_conv3_grad the channels of one depth lie within 2^30 floats: (channels - 1) times their
  * stride + height x width is at most that.  Errors: KATS_EINVAL, KATS_EWORKSPACE, KATS_EHIP. */
 

@@ -562,6 +562,9 @@ int katsevich_rmse_ssim_noscratch(const float *d_f, const float *d_ref, uint64_t
     return KATS_OK;
 }
 
+// Workgroups of 256 threads along x: a launch has less than 2^32 threads there.
+static constexpr int64_t kMostBlocks = ((int64_t)1 << 24) - 1;
+
 // Shape and stride checks of the convolutions; fills the arguments they share.
 static int conv3_args(const char *who, const float *x, const int64_t *xs, const float *y, const int64_t *ys,
                       const int64_t *shape, kats::Conv3Args &a) {
@@ -571,8 +574,9 @@ static int conv3_args(const char *who, const float *x, const int64_t *xs, const 
             return fail(KATS_EINVAL, std::string(who) + ": a size is not in 1 .. 2^31 - 1");
     if (shape[1] > 16 || shape[2] > 16)
         return fail(KATS_EINVAL, std::string(who) + ": more than 16 channels");
-    // grid limits of the launches (65535 in y and z, tiles in x)
-    if (shape[0] > 65535 || shape[3] > 4 * 65535 || ((shape[4] + 7) / 8) * ((shape[5] + 31) / 32) > INT32_MAX / shape[0])
+    // grid limits of the launches (65535 in y and z, tiles in x; the tasks of a batch in an int)
+    const int64_t tiles = ((shape[4] + 7) / 8) * ((shape[5] + 31) / 32);
+    if (shape[0] > 65535 || shape[3] > 4 * 65535 || tiles > kMostBlocks || tiles > INT32_MAX / shape[0])
         return fail(KATS_EINVAL, std::string(who) + ": volume too large");
     // a lane's offset within a depth is 32 bits (the stride of a single channel plays no part)
     const int64_t most = (int64_t)1 << 30;
@@ -639,7 +643,7 @@ int katsevich_stack3(const float *d_x, const int64_t *x_strides, float *d_out, c
     for (int i = 0; i < 5; ++i) {
         if (shape[i] < 1 || shape[i] > INT32_MAX)
             return fail(KATS_EINVAL, "katsevich_stack3: a size is not in 1 .. 2^31 - 1");
-        if (i < 3 && (planes *= shape[i]) > INT32_MAX) return fail(KATS_EINVAL, "katsevich_stack3: volume too large");
+        if (i < 3 && (planes *= shape[i]) > kMostBlocks) return fail(KATS_EINVAL, "katsevich_stack3: volume too large");
     }
     // offsets are 64 bits; the whole output stays below 2^62 bytes
     if (shape[3] * shape[4] > (((int64_t)1 << 58) / planes)) return fail(KATS_EINVAL, "katsevich_stack3: volume too large");
@@ -663,11 +667,11 @@ static int prelu_shape(const int64_t *shape, uint64_t &blocks) {
         if (shape[i] < 1 || shape[i] > INT32_MAX)
             return fail(KATS_EINVAL, "katsevich_prelu_grad: a size is not in 1 .. 2^31 - 1");
         if (i < 3) planes *= (uint64_t)shape[i];
-        if (planes > INT32_MAX) return fail(KATS_EINVAL, "katsevich_prelu_grad: volume too large");
+        if (planes > (uint64_t)kMostBlocks) return fail(KATS_EINVAL, "katsevich_prelu_grad: volume too large");
     }
     const uint64_t n = (uint64_t)shape[3] * (uint64_t)shape[4];
     const uint64_t chunks = (n + (uint64_t)kats::kPreluBlock - 1) / (uint64_t)kats::kPreluBlock;
-    if (chunks > INT32_MAX / planes) return fail(KATS_EINVAL, "katsevich_prelu_grad: volume too large");
+    if (chunks > (uint64_t)kMostBlocks / planes) return fail(KATS_EINVAL, "katsevich_prelu_grad: volume too large");
     blocks = planes * chunks;
     return KATS_OK;
 }

@@ -36,3 +36,38 @@ def test_channel_strides(cin, xc, ok):
     dense = (16 * PLANE, PLANE, 16 * PLANE)
     assert _conv((1, cin, 16, 10, 512, 512), (16 * xc if xc < 1 << 40 else xc, xc, PLANE), dense) == want
     assert _conv((1, 16, cin, 10, 512, 512), dense, (0, xc, PLANE)) == want
+
+
+MANY = 1 << 24
+
+
+@pytest.mark.parametrize("shape,ok", [
+    ((1, 1, MANY - 1, 1, 1), True), ((1, 1, MANY, 1, 1), False), ((1 << 12, 1 << 6, 1 << 6, 1, 1), False),
+    ((MANY // 3, 3, 1, 1, 1), True), ((MANY // 3 + 1, 3, 1, 1, 1), False)])
+def test_launch_limits_of_planes(shape, ok):
+    """A workgroup per plane: less than 2^24 of them, 2^32 threads."""
+    lib = K.load_library()
+    want = EHIP if ok else EINVAL
+    s, n = (c_int64 * 3)(1, 1, 1), (c_int64 * 5)(*shape)
+    assert lib.katsevich_stack3(PTR, s, PTR, n, None) == want
+    assert (lib.katsevich_prelu_scratch_bytes(n) > 0) == ok
+    assert lib.katsevich_prelu_grad(PTR, s, PTR, s, PTR, PTR, s, PTR, n, PTR, c_uint64(1 << 62), None) == want
+
+
+# blocks of 8192 samples: 2 a plane, 2^12 a plane
+@pytest.mark.parametrize("shape,ok", [((1, 1, MANY // 2 - 1, 1, 8193), True), ((1, 1, MANY // 2, 1, 8193), False),
+                                      ((1, 1, (1 << 12) - 1, 1 << 13, 1 << 12), True),
+                                      ((1, 1, 1 << 12, 1 << 13, 1 << 12), False)])
+def test_launch_limits_of_prelu(shape, ok):
+    lib = K.load_library()
+    s, n = (c_int64 * 3)(1, 1, 1), (c_int64 * 5)(*shape)
+    assert (lib.katsevich_prelu_scratch_bytes(n) > 0) == ok
+    assert lib.katsevich_prelu_grad(PTR, s, PTR, s, PTR, PTR, s, PTR, n, PTR, c_uint64(1 << 62),
+                                    None) == (EHIP if ok else EINVAL)
+
+
+@pytest.mark.parametrize("shape,ok", [((1, 1, 1, 1, 8 * (MANY - 1), 1), True), ((1, 1, 1, 1, 8 * MANY, 1), False),
+                                      ((65535, 1, 1, 1, 1, 1), True), ((65536, 1, 1, 1, 1, 1), False),
+                                      ((1, 1, 1, 4 * 65535, 1, 1), True), ((1, 1, 1, 4 * 65535 + 1, 1, 1), False)])
+def test_launch_limits_of_convolutions(shape, ok):
+    assert _conv(shape, (1, 1, 1), (1, 1, 1)) == (EHIP if ok else EINVAL)
