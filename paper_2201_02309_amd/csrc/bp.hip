@@ -14,8 +14,6 @@
 // pitch-relative view m and slice j only: the geometry is bit-identical for every pitch.
 #include "bp_common.hpp"
 
-#include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 #include <vector>
 
@@ -402,7 +400,6 @@ struct BpRequest {
 };
 
 constexpr int kGroupMax = 16;
-constexpr int kBatchRound = 1280;
 struct BpGroup {
     BpRequest r[kGroupMax];
     int n;
@@ -425,8 +422,7 @@ __global__ __launch_bounds__(kNT * TEAMS, TEAMS > 1 ? 1 : bp_waves(KZ, FB, SH::k
 
 }  // namespace
 
-// Kernel instance of a plan: box shape (the first that its largest box fits, kFallback if none
-// does) and polynomial degree.  Runs of 8 and 32 slices have the shapes of their usual boxes only.
+// The box shapes, in the order of kShapeRows and kShapeCols.
 using S32x64 = Shape<64, 32>;      // 16-slice runs of full detectors (clinical: 32 x 44)
 using S64x32 = Shape<32, 64>;      // sparse detectors: few columns, steep slices (49 x 25)
 using S64x64 = Shape<64, 64>;
@@ -435,73 +431,6 @@ using S48x80 = Shape<80, 48>;      // coarse grids under fine detectors (40 x 79
 using S64x80 = Shape<80, 64>;
 using S48x96 = Shape<96, 48>;
 using S48x128 = Shape<128, 48>;
-constexpr int kShapes = 7, kFallback = 7;
-
-constexpr int kShapeRows[kShapes] = {32, 64, 64, 48, 64, 48, 48};
-constexpr int kShapeCols[kShapes] = {64, 32, 64, 80, 80, 96, 128};
-
-static int bp_shape(const KParams &k) {
-    const bool wide = k.bp_kz == 16;
-    const bool has[kShapes] = {k.bp_kz <= 16, wide, k.bp_kz >= 16, wide, wide, wide, wide};
-    for (int i = 0; i < kShapes; ++i)
-        if (has[i] && k.bp_box_rows <= kShapeRows[i] && k.bp_box_cols <= kShapeCols[i]) return i;
-    return kFallback;
-}
-
-// Split of a plan's work over workgroups.  A workgroup walks its hull view by view, which takes
-// 0.5-0.9 us a view however little there is to do, and a CU holds five of them: a grid with few
-// tasks is bound by that chain and leaves CUs idle.  Fewer slices per task make more tasks (each
-// repeating the per-view geometry), more teams shorten the chain.  The measure is the reconstructed
-// voxels in units of a whole 16 x 16 x 16 task; backprojection whole / halves / halves in 4 teams /
-// quarters in 4 teams, us:
-//    60 tasks (64^3, 3 pitches)          361 / 231 / 114 /  84
-//   105 tasks (169^2 x 15)              1044 / 652 / 298 / 413
-//   175 tasks (134^2 x 40)               737 / 495 / 404 / 581
-//   302 tasks (262^2 x 18)               711 / 521 / 596 / 757
-//   304 tasks (512^2 x 10, network)      601 / 485 / 773 / 870
-//   512 tasks (256^2 x 32, boxes 40x79) 1247 / 1462
-//   872 tasks (351^2 x 29)               883 / 911
-// so wide boxes, whose staging every task repeats, are not halved.
-enum { kWhole = 0, kHalves = 1, kHalvesTeams = 2, kQuartersTeams = 3, kSplits = 4 };
-constexpr int kSubs[kSplits] = {1, 2, 2, 4}, kTeams[kSplits] = {1, 1, 4, 4};
-
-// Dynamic LDS: the teams' box buffers, and their sums at the end
-static unsigned bp_bytes(int teams, int pitch, int rows, int kz) {
-    const unsigned boxes = (unsigned)teams * 2u * (unsigned)pitch * (unsigned)rows * 4u;
-    const unsigned sums = (unsigned)(teams - 1) * (unsigned)kz * kNT * 4u;
-    return boxes > sums ? boxes : sums;
-}
-constexpr unsigned kLdsBytes = 163840;     // of a CU (gfx950)
-
-struct BpClass {
-    int shape, split, poly4;
-    bool operator==(const BpClass &o) const { return shape == o.shape && split == o.split && poly4 == o.poly4; }
-};
-
-static BpClass kernel_class(const KParams &k) {
-    BpClass c;
-    c.shape = bp_shape(k);
-    c.poly4 = (k.atan_deg >= 0 && k.atan_deg <= 4) ? 1 : 0;
-    c.split = kWhole;
-    if (k.bp_kz != 16) return c;
-    const long long full = k.n_valid / ((long long)kT * kT * 16);
-    // Layers and workgroups that have slices.  A team workgroup fills a CU, so a thin volume, which has
-    // many workgroups for its voxels, keeps single ones, and whole ones where halves would be empty.
-    // Reconstruction whole / halves / halves in 4 teams, us: 356^2 x 5 (495 workgroups) 340 / 348 / 378,
-    // 300^2 x 10 (352) 374 / 340 / 377, 256^2 x 12 (256) 379 / 314 / 287
-    const long long last = k.nz - (long long)(k.n_pitches - 1) * k.ns;
-    const long long layers = (k.n_pitches - 1) * ((k.ns + 15ll) / 16) + (last + 15) / 16;
-    const bool many = k.n_valid / (kT * kT) * layers >= 300ll * k.nz;
-    if (full < 80) c.split = kQuartersTeams;
-    else if (full < 220 && !many) c.split = kHalvesTeams;
-    else if (full < 450 && c.shape <= 1 && k.nz > 8 * layers) c.split = kHalves;
-    // (the widest shape: 136 floats, 38 rows and more do not fit four times)
-    if (kTeams[c.split] > 1 && c.shape < kFallback && bp_bytes(kTeams[c.split], kShapeCols[c.shape] + 8, k.bp_box_rows < 32 ? 32 : k.bp_box_rows, 0) + 64 > kLdsBytes)
-        c.split = kHalves;
-    if (c.split != kWhole) c.poly4 = 0;    // one instance each: the longer polynomial's further terms are 0
-    return c;
-}
-
 // f(instance tag) for the class's template arguments
 template <int KZ_, class SH_, bool FB_, bool P4_, int SUB_, int TEAMS_>
 struct BpInst {
@@ -567,42 +496,6 @@ hipError_t launch_backproject(const KParams &k, const float *gF, float *vol, hip
                            boxes, rows);
     });
     return hipGetLastError();
-}
-
-// The instance of every request of a batch: its own, but a shape with less than a round of tasks (five
-// per CU) joins another one, in the first shape that takes both: alone it would end the batch with
-// a launch that leaves CUs idle.  Two requests of 1536 and 512 tasks with boxes of 31 x 79 and 50 x 79,
-// filter included: 5.60 ms joined, 6.97 apart with the second on the HBM path.  The shape does not change a result's bits; the split does, so only requests of one split
-// and one team join.
-static std::vector<BpClass> batch_classes(const KParams *ks, int n) {
-    std::vector<BpClass> cls(n);
-    for (int i = 0; i < n; ++i) cls[i] = kernel_class(ks[i]);
-    for (int split = 0; split < kSplits; ++split)
-        for (int poly4 = 0; poly4 < 2 && kTeams[split] == 1; ++poly4) {
-            for (int shape = 0; shape <= kShapes; ++shape) {
-                long long tasks[kShapes + 1] = {};
-                for (int i = 0; i < n; ++i)
-                    if (cls[i].split == split && cls[i].poly4 == poly4)
-                        tasks[cls[i].shape] += (long long)ks[i].bp_tiles_x * ks[i].bp_tiles_y * ks[i].n_pitches * ks[i].bp_runs * kSubs[split];
-                if (tasks[shape] == 0 || tasks[shape] >= kBatchRound) continue;
-                int other = -1;
-                for (int t = 0; t <= kShapes; ++t)
-                    if (t != shape && tasks[t] > 0 && (other < 0 || std::abs(t - shape) < std::abs(other - shape))) other = t;
-                if (other < 0) continue;
-                KParams both = ks[0];
-                both.bp_box_rows = both.bp_box_cols = 0;
-                auto in = [&](int i) { return cls[i].split == split && cls[i].poly4 == poly4 && (cls[i].shape == shape || cls[i].shape == other); };
-                for (int i = 0; i < n; ++i)
-                    if (in(i)) {
-                        both.bp_box_rows = std::max(both.bp_box_rows, ks[i].bp_box_rows);
-                        both.bp_box_cols = std::max(both.bp_box_cols, ks[i].bp_box_cols);
-                    }
-                const int joined = bp_shape(both);
-                for (int i = 0; i < n; ++i)
-                    if (in(i)) cls[i].shape = joined;
-            }
-        }
-    return cls;
 }
 
 // Requests are grouped by kernel instance (box shape, split, polynomial degree); each launch takes

@@ -32,8 +32,6 @@ using namespace bpdev;
 // taps to HBM atomics; the kernel's time for the 256 x 256 x 64 sparse-detector workload, whose
 // boxes are 49 x 25 cells, went from 50.4 to 7.5 ms, and with 40 x 79 boxes (256 x 256 x 32,
 // 736 columns, fixed point) from 12.1 to 5.6 ms.
-constexpr unsigned kLdsBytes = 163840;    // per CU and workgroup on gfx950
-
 // One box buffer: rows x pitch accumulators.
 struct BpTShape {
     int pitch, rows;
@@ -456,30 +454,6 @@ BpTShape bpT_shape(const KParams &k, bool &fb, unsigned &bytes) {
     bytes = size(s);
     return s;
 }
-
-// Tasks that the views of a (tile, run) hull are split over.  A workgroup walks its hull view by
-// view at 3-4 us a view, so few tasks leave CUs idle behind that chain, and a last round of long
-// tasks does on larger grids; the boxes' sums meet in g^F-bar anyway.  Whole adjoint by reconstructed
-// voxels in units of 16 x 16 x 16 tasks, parts 1 / 4 / 8 / 16 / 32, us:
-//      4 (54^2 x 7)             1716 /  571 /  358 /  242 /  187
-//     59 (64^3)                 1376 /  458 /  357 /  312 /  281
-//    104 (169^2 x 15)           4224 / 1375 / 1290 / 1160 / 1102
-//    304 (512^2 x 10, network)  2864 / 2302 / 2228 / 2238 / 2364
-//    512 (256^2 x 32)           6023 / 5535 / 5561 / 5601 / 5756
-//   1024 (256^2 x 64, sparse)   8265 / 7511 / 7328 / 7325 / 7461
-//   8192 (512^2 x 128)         42916 / 42898 (42589 in 2) / 43636
-int bpT_parts(const KParams &k) {
-    const long long full = k.n_valid / ((long long)kT * kT * 16);
-    return full < 60 ? 32 : (full < 250 ? 16 : (full < 1500 ? 8 : (full < 6000 ? 4 : 2)));
-}
-
-// Whether the rows' sums are kept in a window common to the wave (WIN).  It takes half of the LDS
-// atomics' instructions and fewer operations, but its lanes reach one column's cells together
-// where the slice-by-slice walk has turned their slices against each other, so it pays only where
-// boxes are wide enough to keep the lanes apart: whole adjoint, walk / window, 512^2 x 10 network pitch
-// (boxes 20 x 57) 2.22 / 1.66 ms, 256^2 x 32 (40 x 79) 5.54 / 5.20, 128^2 x 8 (20 x 217) 0.51 / 0.40,
-// clinical (32 x 44) 42.7 / 47.7, 256^2 x 64 sparse (49 x 25) 7.3 / 13.0.
-bool bpT_window(const KParams &k) { return k.bp_box_cols > 50; }
 
 template <int KZ, bool DET>
 void launch_bpT(const KParams &k, hipStream_t s, const float *gvol, void *gFout, const double *fscale) {

@@ -1,0 +1,190 @@
+// Which kernel instance, split and order of tiles the backprojector (bp.hip) and its adjoint
+// (bp_adjoint.hip) take for a plan, and which plans of a batch share a launch.  Host code, apart from
+// the order of the tiles.
+#pragma once
+
+#include <algorithm>
+#include <cstdlib>
+#include <vector>
+
+#include "kernels.hpp"
+
+namespace kats {
+namespace bpdev {
+
+constexpr int kT = kBpTile;               // 16
+constexpr int kNT = kT * kT;              // lanes of a tile's workgroup
+constexpr unsigned kLdsBytes = 163840;    // per CU and workgroup on gfx950
+
+// Tile of block l (0 .. tiles - 1) of layer z of a launch whose layers (slice runs, pitches, parts)
+// of tiles_x x tiles_y tiles follow one another; first: the launch's block index of the layer's
+// first block.
+//
+// Blocks go to the eight XCDs in turn, each with an L2 of its own, so with neighbouring tiles side
+// by side in the grid every XCD reads the whole filtered window of every layer.  In layers of at least
+// `least` tiles (kXcdForward, kXcdAdjoint) the blocks of one XCD take a compact part instead: the tiles are numbered along bands
+// of a quarter of the rows, column by column, each quarter of the numbering is cut into eight
+// segments, and XCD x takes segment x + z + quarter.  Parts differ in work (corners outside the field
+// of view) and an XCD cannot take work from another, hence four quarters a layer, and the turn from
+// layer to layer.  512 x 512 x 128: HBM reads of the backprojection 14.2 -> 4.5 GB, whole
+// reconstruction 10.46 -> 10.08 ms, whole adjoint 42.5 -> 41.8 ms; 512 x 512 x 10 (network), forward and
+// adjoint 2.25 -> 1.90 ms.  Smaller layers read little, and their fewer blocks show what balance is
+// lost.  Plain order / this one by tiles, ms:
+//   forward   529, one layer (356^2 x 5): 0.340 / 0.354   256: 4.52 / 4.48   361 (301^2 x 77): 3.00 / 3.04   400: 4.87 / 4.83   576: 3.80 / 3.74
+//             784: 4.90 / 4.75   1024 (512^2 x 32): 3.29 / 3.20
+//   adjoint   256 (sparse): 18.70 / 18.95   400: 14.74 / 14.70   576: 12.88 / 12.98   784: 16.41 / 16.57
+//             1024: 11.68 / 11.15
+constexpr unsigned kXcdForward = 768, kXcdAdjoint = 1024;      // least tiles
+struct TileAt {
+    int x, y;
+};
+__host__ __device__ inline TileAt xcd_tile(unsigned least, int tiles_x, int tiles_y, unsigned l, unsigned z,
+                                           unsigned first) {
+    const unsigned tiles = (unsigned)tiles_x * (unsigned)tiles_y;
+    if (tiles < least) return {(int)(l % (unsigned)tiles_x), (int)(l / (unsigned)tiles_x)};
+    const unsigned chunk = (tiles / 4 + 7) / 8 * 8;
+    const unsigned c = l / chunk, at = c * chunk;               // chunk: a multiple of 8, so l - at keeps l's XCD
+    const unsigned n = tiles - at < chunk ? tiles - at : chunk; // tiles of this chunk
+    const unsigned r = (l - at) & 7, i = (l - at) >> 3;         // the i-th block of its XCD in the chunk
+    const unsigned turn = (first + z + c) & 7, seg = (r + turn) & 7;
+    // blocks of remainder below n % 8 are one more: segments before seg that belong to such
+    const unsigned more = (1u << (n & 7)) - 1u;
+    const unsigned longer = ((more << turn) | (more >> (8 - turn))) & ((1u << seg) - 1u);
+    const unsigned q = at + seg * (n >> 3) + (unsigned)__builtin_popcount(longer) + i;
+    const unsigned high = ((unsigned)tiles_y + 3) / 4, band = q / (high * tiles_x), rest = q - band * high * tiles_x;
+    const unsigned below = (unsigned)tiles_y - band * high, rows = below < high ? below : high;
+    return {(int)(rest / rows), (int)(band * high + rest % rows)};
+}
+
+// Kernel instance of a plan: box shape (the first that its largest box fits, kFallback if none
+// does) and polynomial degree.  Runs of 8 and 32 slices have the shapes of their usual boxes only.
+constexpr int kShapes = 7, kFallback = 7;
+
+constexpr int kShapeRows[kShapes] = {32, 64, 64, 48, 64, 48, 48};
+constexpr int kShapeCols[kShapes] = {64, 32, 64, 80, 80, 96, 128};
+
+inline int bp_shape(const KParams &k) {
+    const bool wide = k.bp_kz == 16;
+    const bool has[kShapes] = {k.bp_kz <= 16, wide, k.bp_kz >= 16, wide, wide, wide, wide};
+    for (int i = 0; i < kShapes; ++i)
+        if (has[i] && k.bp_box_rows <= kShapeRows[i] && k.bp_box_cols <= kShapeCols[i]) return i;
+    return kFallback;
+}
+
+// Split of a plan's work over workgroups.  A workgroup walks its hull view by view, which takes
+// 0.5-0.9 us a view however little there is to do, and a CU holds five of them: a grid with few
+// tasks is bound by that chain and leaves CUs idle.  Fewer slices per task make more tasks (each
+// repeating the per-view geometry), more teams shorten the chain.  The measure is the reconstructed
+// voxels in units of a whole 16 x 16 x 16 task; backprojection whole / halves / halves in 4 teams /
+// quarters in 4 teams, us:
+//    60 tasks (64^3, 3 pitches)          361 / 231 / 114 /  84
+//   105 tasks (169^2 x 15)              1044 / 652 / 298 / 413
+//   175 tasks (134^2 x 40)               737 / 495 / 404 / 581
+//   302 tasks (262^2 x 18)               711 / 521 / 596 / 757
+//   304 tasks (512^2 x 10, network)      601 / 485 / 773 / 870
+//   512 tasks (256^2 x 32, boxes 40x79) 1247 / 1462
+//   872 tasks (351^2 x 29)               883 / 911
+// so wide boxes, whose staging every task repeats, are not halved.
+enum { kWhole = 0, kHalves = 1, kHalvesTeams = 2, kQuartersTeams = 3, kSplits = 4 };
+constexpr int kSubs[kSplits] = {1, 2, 2, 4}, kTeams[kSplits] = {1, 1, 4, 4};
+
+// Dynamic LDS: the teams' box buffers, and their sums at the end
+inline unsigned bp_bytes(int teams, int pitch, int rows, int kz) {
+    const unsigned boxes = (unsigned)teams * 2u * (unsigned)pitch * (unsigned)rows * 4u;
+    const unsigned sums = (unsigned)(teams - 1) * (unsigned)kz * kNT * 4u;
+    return boxes > sums ? boxes : sums;
+}
+
+struct BpClass {
+    int shape, split, poly4;
+    bool operator==(const BpClass &o) const { return shape == o.shape && split == o.split && poly4 == o.poly4; }
+};
+
+inline BpClass kernel_class(const KParams &k) {
+    BpClass c;
+    c.shape = bp_shape(k);
+    c.poly4 = (k.atan_deg >= 0 && k.atan_deg <= 4) ? 1 : 0;
+    c.split = kWhole;
+    if (k.bp_kz != 16) return c;
+    const long long full = k.n_valid / ((long long)kT * kT * 16);
+    // Layers and workgroups that have slices.  A team workgroup fills a CU, so a thin volume, which has
+    // many workgroups for its voxels, keeps single ones, and whole ones where halves would be empty.
+    // Reconstruction whole / halves / halves in 4 teams, us: 356^2 x 5 (495 workgroups) 340 / 348 / 378,
+    // 300^2 x 10 (352) 374 / 340 / 377, 256^2 x 12 (256) 379 / 314 / 287
+    const long long last = k.nz - (long long)(k.n_pitches - 1) * k.ns;
+    const long long layers = (k.n_pitches - 1) * ((k.ns + 15ll) / 16) + (last + 15) / 16;
+    const bool many = k.n_valid / (kT * kT) * layers >= 300ll * k.nz;
+    if (full < 80) c.split = kQuartersTeams;
+    else if (full < 220 && !many) c.split = kHalvesTeams;
+    else if (full < 450 && c.shape <= 1 && k.nz > 8 * layers) c.split = kHalves;
+    // (the widest shape: 136 floats, 38 rows and more do not fit four times)
+    if (kTeams[c.split] > 1 && c.shape < kFallback && bp_bytes(kTeams[c.split], kShapeCols[c.shape] + 8, k.bp_box_rows < 32 ? 32 : k.bp_box_rows, 0) + 64 > kLdsBytes)
+        c.split = kHalves;
+    if (c.split != kWhole) c.poly4 = 0;    // one instance each: the longer polynomial's further terms are 0
+    return c;
+}
+
+constexpr int kBatchRound = 1280;          // tasks of one round: five per CU
+
+// The instance of every request of a batch: its own, but a shape with less than a round of tasks (five
+// per CU) joins another one, in the first shape that takes both: alone it would end the batch with
+// a launch that leaves CUs idle.  Two requests of 1536 and 512 tasks with boxes of 31 x 79 and 50 x 79,
+// filter included: 5.60 ms joined, 6.97 apart with the second on the HBM path.  The shape does not change a result's bits; the split does, so only requests of one split
+// and one team join.
+inline std::vector<BpClass> batch_classes(const KParams *ks, int n) {
+    std::vector<BpClass> cls(n);
+    for (int i = 0; i < n; ++i) cls[i] = kernel_class(ks[i]);
+    for (int split = 0; split < kSplits; ++split)
+        for (int poly4 = 0; poly4 < 2 && kTeams[split] == 1; ++poly4) {
+            for (int shape = 0; shape <= kShapes; ++shape) {
+                long long tasks[kShapes + 1] = {};
+                for (int i = 0; i < n; ++i)
+                    if (cls[i].split == split && cls[i].poly4 == poly4)
+                        tasks[cls[i].shape] += (long long)ks[i].bp_tiles_x * ks[i].bp_tiles_y * ks[i].n_pitches * ks[i].bp_runs * kSubs[split];
+                if (tasks[shape] == 0 || tasks[shape] >= kBatchRound) continue;
+                int other = -1;
+                for (int t = 0; t <= kShapes; ++t)
+                    if (t != shape && tasks[t] > 0 && (other < 0 || std::abs(t - shape) < std::abs(other - shape))) other = t;
+                if (other < 0) continue;
+                KParams both = ks[0];
+                both.bp_box_rows = both.bp_box_cols = 0;
+                auto in = [&](int i) { return cls[i].split == split && cls[i].poly4 == poly4 && (cls[i].shape == shape || cls[i].shape == other); };
+                for (int i = 0; i < n; ++i)
+                    if (in(i)) {
+                        both.bp_box_rows = std::max(both.bp_box_rows, ks[i].bp_box_rows);
+                        both.bp_box_cols = std::max(both.bp_box_cols, ks[i].bp_box_cols);
+                    }
+                const int joined = bp_shape(both);
+                for (int i = 0; i < n; ++i)
+                    if (in(i)) cls[i].shape = joined;
+            }
+        }
+    return cls;
+}
+
+// Tasks that the views of a (tile, run) hull are split over.  A workgroup walks its hull view by
+// view at 3-4 us a view, so few tasks leave CUs idle behind that chain, and a last round of long
+// tasks does on larger grids; the boxes' sums meet in g^F-bar anyway.  Whole adjoint by reconstructed
+// voxels in units of 16 x 16 x 16 tasks, parts 1 / 4 / 8 / 16 / 32, us:
+//      4 (54^2 x 7)             1716 /  571 /  358 /  242 /  187
+//     59 (64^3)                 1376 /  458 /  357 /  312 /  281
+//    104 (169^2 x 15)           4224 / 1375 / 1290 / 1160 / 1102
+//    304 (512^2 x 10, network)  2864 / 2302 / 2228 / 2238 / 2364
+//    512 (256^2 x 32)           6023 / 5535 / 5561 / 5601 / 5756
+//   1024 (256^2 x 64, sparse)   8265 / 7511 / 7328 / 7325 / 7461
+//   8192 (512^2 x 128)         42916 / 42898 (42589 in 2) / 43636
+inline int bpT_parts(const KParams &k) {
+    const long long full = k.n_valid / ((long long)kT * kT * 16);
+    return full < 60 ? 32 : (full < 250 ? 16 : (full < 1500 ? 8 : (full < 6000 ? 4 : 2)));
+}
+
+// Whether the rows' sums are kept in a window common to the wave (WIN).  It takes half of the LDS
+// atomics' instructions and fewer operations, but its lanes reach one column's cells together
+// where the slice-by-slice walk has turned their slices against each other, so it pays only where
+// boxes are wide enough to keep the lanes apart: whole adjoint, walk / window, 512^2 x 10 network pitch
+// (boxes 20 x 57) 2.22 / 1.66 ms, 256^2 x 32 (40 x 79) 5.54 / 5.20, 128^2 x 8 (20 x 217) 0.51 / 0.40,
+// clinical (32 x 44) 42.7 / 47.7, 256^2 x 64 sparse (49 x 25) 7.3 / 13.0.
+inline bool bpT_window(const KParams &k) { return k.bp_box_cols > 50; }
+
+}  // namespace bpdev
+}  // namespace kats
