@@ -4,7 +4,6 @@
 #pragma once
 
 #include <algorithm>
-#include <cstdlib>
 #include <vector>
 
 #include "kernels.hpp"
@@ -58,7 +57,7 @@ __host__ __device__ inline TileAt xcd_tile(unsigned least, int tiles_x, int tile
 
 // Kernel instance of a plan: box shape (the first that its largest box fits, kFallback if none
 // does) and polynomial degree.  Runs of 8 and 32 slices have the shapes of their usual boxes only.
-constexpr int kShapes = 7, kFallback = 7;
+constexpr int kShapes = 7, kShape48x80 = 3, kFallback = 7;
 
 constexpr int kShapeRows[kShapes] = {32, 64, 64, 48, 64, 48, 48};
 constexpr int kShapeCols[kShapes] = {64, 32, 64, 80, 80, 96, 128};
@@ -128,35 +127,51 @@ constexpr int kBatchRound = 1280;          // tasks of one round: five per CU
 
 // The instance of every request of a batch: its own, but a shape with less than a round of tasks (five
 // per CU) joins another one, in the first shape that takes both: alone it would end the batch with
-// a launch that leaves CUs idle.  Two requests of 1536 and 512 tasks with boxes of 31 x 79 and 50 x 79,
-// filter included: 5.60 ms joined, 6.97 apart with the second on the HBM path.  The shape does not change a result's bits; the split does, so only requests of one split
-// and one team join.
+// a launch that leaves CUs idle.  Joining costs the other class where the new shape is slower for it,
+// so one that changes to another shape than S48x80 (as many workgroups per CU) joins up to two rounds
+// of its tasks, and none joins on the HBM path.  Backprojection apart / joined, ms:
+//    2048 tasks of 32 x 44 boxes and  512 of 28 x 79, in S48x80        3.49 / 3.00
+//    4096                        and  512 of 28 x 79                   5.56 / 5.02
+//   10240                        and  512 of 28 x 79                   9.82 / 9.73
+//    2048 tasks of 32 x 44       and  512 of 58 x 46, in S64x64        3.88 / 3.83
+//    4096                        and  512 of 58 x 46                   5.98 / 6.14
+//   10240                        and  768 of 49 x 25                  10.07 / 10.56
+//    2048 tasks of 32 x 44       and  512 of 53 x 79, in S64x80        3.84 / 3.80
+//    4096                        and  512 of 53 x 79                   5.97 / 6.00
+//   10240                        and  512 of 53 x 79                  10.21 / 11.28
+//    1536 tasks of 49 x 79       and  512 of 28 x 79, in S64x80        3.88 / 3.10
+//     768 tasks of 49 x 25       and  676 of 42 x 103, on the HBM path 2.64 / 3.01
+// The shape does not change a result's bits; the split does, so only requests of one split and one
+// team join.
 inline std::vector<BpClass> batch_classes(const KParams *ks, int n) {
     std::vector<BpClass> cls(n);
     for (int i = 0; i < n; ++i) cls[i] = kernel_class(ks[i]);
     for (int split = 0; split < kSplits; ++split)
         for (int poly4 = 0; poly4 < 2 && kTeams[split] == 1; ++poly4) {
-            for (int shape = 0; shape <= kShapes; ++shape) {
+            for (int shape = 0; shape < kShapes; ++shape) {
                 long long tasks[kShapes + 1] = {};
                 for (int i = 0; i < n; ++i)
                     if (cls[i].split == split && cls[i].poly4 == poly4)
                         tasks[cls[i].shape] += (long long)ks[i].bp_tiles_x * ks[i].bp_tiles_y * ks[i].n_pitches * ks[i].bp_runs * kSubs[split];
                 if (tasks[shape] == 0 || tasks[shape] >= kBatchRound) continue;
-                int other = -1;
-                for (int t = 0; t <= kShapes; ++t)
-                    if (t != shape && tasks[t] > 0 && (other < 0 || std::abs(t - shape) < std::abs(other - shape))) other = t;
-                if (other < 0) continue;
-                KParams both = ks[0];
-                both.bp_box_rows = both.bp_box_cols = 0;
-                auto in = [&](int i) { return cls[i].split == split && cls[i].poly4 == poly4 && (cls[i].shape == shape || cls[i].shape == other); };
-                for (int i = 0; i < n; ++i)
-                    if (in(i)) {
-                        both.bp_box_rows = std::max(both.bp_box_rows, ks[i].bp_box_rows);
-                        both.bp_box_cols = std::max(both.bp_box_cols, ks[i].bp_box_cols);
-                    }
-                const int joined = bp_shape(both);
-                for (int i = 0; i < n; ++i)
-                    if (in(i)) cls[i].shape = joined;
+                // the nearest shape whose class may be joined
+                for (int step = 1, joined = kFallback; step < 2 * kShapes && joined == kFallback; ++step) {
+                    const int other = shape + (step & 1 ? -(step + 1) / 2 : step / 2);
+                    if (other < 0 || other >= kShapes || tasks[other] == 0) continue;
+                    auto in = [&](int i) { return cls[i].split == split && cls[i].poly4 == poly4 && (cls[i].shape == shape || cls[i].shape == other); };
+                    KParams both = ks[0];
+                    both.bp_box_rows = both.bp_box_cols = 0;
+                    for (int i = 0; i < n; ++i)
+                        if (in(i)) {
+                            both.bp_box_rows = std::max(both.bp_box_rows, ks[i].bp_box_rows);
+                            both.bp_box_cols = std::max(both.bp_box_cols, ks[i].bp_box_cols);
+                        }
+                    joined = bp_shape(both);
+                    if (joined != other && joined != kShape48x80 && tasks[other] > 2 * kBatchRound) joined = kFallback;
+                    if (joined == kFallback) continue;
+                    for (int i = 0; i < n; ++i)
+                        if (in(i)) cls[i].shape = joined;
+                }
             }
         }
     return cls;

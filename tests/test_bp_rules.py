@@ -31,3 +31,37 @@ def rules(tmp_path_factory):
                                    (35, 37), (41, 25), (64, 64), (130, 7)])
 def test_every_tile_once(rules, tx, ty):
     assert rules(*(f"order {tx} {ty} 9 {least}" for least in (768, 1024, 1))) == [["ok"]] * 3
+
+
+# shapes 32x64, 64x32, 64x64, 48x80, 64x80, 48x96, 48x128, then the HBM path (7)
+PLANS = {"clinical": (32, 44, 32, 4), "half-clinical": (32, 44, 32, 2), "quarter-clinical": (32, 44, 32, 1),
+         "sparse": (49, 25, 16, 3), "wide": (42, 103, 13, 4), "flat": (28, 79, 16, 2), "square": (58, 46, 16, 2),
+         "tall": (53, 79, 16, 2), "long": (49, 79, 16, 6), "far": (70, 140, 16, 2)}
+
+
+def _plan(name):
+    """16-slice runs of full tiles, every voxel valid; a plan of `layers` 16-slice layers."""
+    rows, cols, tiles, layers = PLANS[name]
+    layers = {"clinical": 10, "half-clinical": 4, "quarter-clinical": 2}.get(name, layers)
+    return (f"plan {name} 16 {rows} {cols} 4 {tiles * tiles * 256 * layers * 16} {tiles} {tiles} {16 * layers} "
+            f"{16 * layers} 1 {layers}")
+
+
+@pytest.mark.parametrize("names,shapes", [
+    # no launch of an LDS shape is moved to the HBM path
+    (("sparse", "wide"), (1, 6)), (("wide", "sparse"), (6, 1)), (("square", "wide"), (2, 6)),
+    (("flat", "far"), (3, 7)), (("far", "far"), (7, 7)),
+    # the nearest shape that can be joined, past one that cannot
+    (("sparse", "wide", "tall"), (4, 6, 4)), (("flat", "wide", "square"), (4, 6, 4)),
+    # a class of many tasks keeps its shape unless the new one serves it as well
+    (("clinical", "sparse"), (0, 1)), (("half-clinical", "square"), (0, 2)), (("clinical", "tall"), (0, 4)),
+    (("half-clinical", "tall"), (0, 4)), (("clinical", "flat"), (3, 3)),
+    # few tasks join
+    (("quarter-clinical", "flat"), (3, 3)), (("quarter-clinical", "square"), (2, 2)),
+    (("quarter-clinical", "tall"), (4, 4)), (("long", "flat"), (4, 4)), (("half-clinical", "flat"), (3, 3))])
+def test_batches(rules, names, shapes):
+    out = rules(*(_plan(n) for n in set(names)), *(f"class {n}" for n in names), "batch " + " ".join(names))
+    alone, got = out[:-1], [out[-1][i:i + 3] for i in range(0, len(out[-1]), 3)]
+    # splits and polynomials, which decide the bits, stay as they are alone
+    assert [c[1:] for c in got] == [c[1:] for c in alone] == [["0", "1"]] * len(names)
+    assert tuple(int(c[0]) for c in got) == shapes
