@@ -108,12 +108,19 @@ inline BpClass kernel_class(const KParams &k) {
     const long long full = k.n_valid / ((long long)kT * kT * 16);
     // Layers and workgroups that have slices.  A team workgroup fills a CU, so a thin volume, which has
     // many workgroups for its voxels, keeps single ones, and whole ones where halves would be empty.
-    // Reconstruction whole / halves / halves in 4 teams, us: 356^2 x 5 (495 workgroups) 340 / 348 / 378,
-    // 300^2 x 10 (352) 374 / 340 / 377, 256^2 x 12 (256) 379 / 314 / 287
+    // Backprojection whole / halves / halves in 4 teams / quarters in 4 teams, us, by workgroups that have
+    // voxels:
+    //   1024 (512^2 x 1)   337 / 320 / 410 / 390
+    //    624 (400^2 x 1)   299 / 288 / 303 / 281      400^2 x 4  324 / 315 / 346 / 321
+    //    493 (356^2 x 5)   372 / 365 / 391 / 469
+    //    352 (300^2 x 10)  374 / 340 / 377 (whole reconstruction)
+    //    348 (300^2 x 2)   271 / 265 / 219 / 203
+    //    256 (256^2 x 4)   277 / 248 / 129 / 119      256^2 x 12 459 / 320 / 281 / 342
     const long long last = k.nz - (long long)(k.n_pitches - 1) * k.ns;
     const long long layers = (k.n_pitches - 1) * ((k.ns + 15ll) / 16) + (last + 15) / 16;
-    const bool many = k.n_valid / (kT * kT) * layers >= 300ll * k.nz;
-    if (full < 80) c.split = kQuartersTeams;
+    const long long groups = k.n_valid / (kT * kT) * layers / std::max(k.nz, 1);
+    const bool many = groups >= 300;
+    if (full < 80 && groups < 700) c.split = kQuartersTeams;
     else if (full < 220 && !many) c.split = kHalvesTeams;
     else if (full < 450 && c.shape <= 1 && k.nz > 8 * layers) c.split = kHalves;
     // (the widest shape: 136 floats, 38 rows and more do not fit four times)

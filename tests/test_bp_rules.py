@@ -65,3 +65,15 @@ def test_batches(rules, names, shapes):
     # splits and polynomials, which decide the bits, stay as they are alone
     assert [c[1:] for c in got] == [c[1:] for c in alone] == [["0", "1"]] * len(names)
     assert tuple(int(c[0]) for c in got) == shapes
+
+
+# voxels across, slices; whether teams of 256 lanes share a task's views
+@pytest.mark.parametrize("nxy,nz,teams", [(512, 1, False), (512, 2, False), (480, 1, False), (448, 1, True), (400, 1, True),
+                                          (400, 2, True), (304, 4, True), (320, 4, False), (256, 4, True),
+                                          (256, 12, True), (352, 5, False), (64, 64, True), (96, 16, True)])
+def test_thin_volumes(rules, nxy, nz, teams):
+    """Layers of many workgroups keep single ones however few their voxels are."""
+    tiles = nxy // 16
+    line = f"plan p 16 15 24 4 {tiles * tiles * 256 * nz * 4 // 5} {tiles} {tiles} {nz} 49 {-(-nz // 49)} {-(-min(nz, 49) // 16)}"
+    split = rules(line, "class p")[0][1]
+    assert (split in ("2", "3")) == teams
