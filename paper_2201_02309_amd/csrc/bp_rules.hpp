@@ -84,8 +84,8 @@ inline int bp_shape(const KParams &k) {
 //   512 tasks (256^2 x 32, boxes 40x79) 1247 / 1462
 //   872 tasks (351^2 x 29)               883 / 911
 // so wide boxes, whose staging every task repeats, are not halved.
-enum { kWhole = 0, kHalves = 1, kHalvesTeams = 2, kQuartersTeams = 3, kSplits = 4 };
-constexpr int kSubs[kSplits] = {1, 2, 2, 4}, kTeams[kSplits] = {1, 1, 4, 4};
+enum { kWhole = 0, kHalves = 1, kHalvesTeams = 2, kQuartersTeams = 3, kThin = 4, kSplits = 5 };
+constexpr int kSubs[kSplits] = {1, 2, 2, 4, 1}, kTeams[kSplits] = {1, 1, 4, 4, 1};
 
 // Dynamic LDS: the teams' box buffers, and their sums at the end
 inline unsigned bp_bytes(int teams, int pitch, int rows, int kz) {
@@ -107,15 +107,15 @@ inline BpClass kernel_class(const KParams &k) {
     if (k.bp_kz != 16) return c;
     const long long full = k.n_valid / ((long long)kT * kT * 16);
     // Layers and workgroups that have slices.  A team workgroup fills a CU, so a thin volume, which has
-    // many workgroups for its voxels, keeps single ones, and whole ones where halves would be empty.
-    // Backprojection whole / halves / halves in 4 teams / quarters in 4 teams, us, by workgroups that have
-    // voxels:
-    //   1024 (512^2 x 1)   337 / 320 / 410 / 390
-    //    624 (400^2 x 1)   299 / 288 / 303 / 281      400^2 x 4  324 / 315 / 346 / 321
-    //    493 (356^2 x 5)   372 / 365 / 391 / 469
+    // many workgroups for its voxels, keeps single ones, and whole ones where halves would be empty: of 8
+    // slices where no layer has more and the box is the small one.  Backprojection whole / halves /
+    // halves in 4 teams / quarters in 4 teams / whole of 8 slices, us, by workgroups that have voxels:
+    //   1024 (512^2 x 1)   337 / 320 / 410 / 390 / 302
+    //    624 (400^2 x 1)   299 / 288 / 303 / 281 / 269      400^2 x 4  324 / 315 / 346 / 321 / 295
+    //    493 (356^2 x 5)   372 / 365 / 391 / 469 / 349
     //    352 (300^2 x 10)  374 / 340 / 377 (whole reconstruction)
     //    348 (300^2 x 2)   271 / 265 / 219 / 203
-    //    256 (256^2 x 4)   277 / 248 / 129 / 119      256^2 x 12 459 / 320 / 281 / 342
+    //    256 (256^2 x 4)   277 / 248 / 129 / 119            256^2 x 12 459 / 320 / 281 / 342
     const long long last = k.nz - (long long)(k.n_pitches - 1) * k.ns;
     const long long layers = (k.n_pitches - 1) * ((k.ns + 15ll) / 16) + (last + 15) / 16;
     const long long groups = k.n_valid / (kT * kT) * layers / std::max(k.nz, 1);
@@ -126,7 +126,8 @@ inline BpClass kernel_class(const KParams &k) {
     // (the widest shape: 136 floats, 38 rows and more do not fit four times)
     if (kTeams[c.split] > 1 && c.shape < kFallback && bp_bytes(kTeams[c.split], kShapeCols[c.shape] + 8, k.bp_box_rows < 32 ? 32 : k.bp_box_rows, 0) + 64 > kLdsBytes)
         c.split = kHalves;
-    if (c.split != kWhole) c.poly4 = 0;    // one instance each: the longer polynomial's further terms are 0
+    if (c.split == kWhole && c.shape == 0 && std::min(k.ns, k.nz) <= 8) c.split = kThin;
+    if (c.split != kWhole && c.split != kThin) c.poly4 = 0;    // one instance each: the longer polynomial's further terms are 0
     return c;
 }
 

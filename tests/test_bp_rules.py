@@ -77,3 +77,13 @@ def test_thin_volumes(rules, nxy, nz, teams):
     line = f"plan p 16 15 24 4 {tiles * tiles * 256 * nz * 4 // 5} {tiles} {tiles} {nz} 49 {-(-nz // 49)} {-(-min(nz, 49) // 16)}"
     split = rules(line, "class p")[0][1]
     assert (split in ("2", "3")) == teams
+
+
+@pytest.mark.parametrize("nz,box,split", [(1, "15 24", "4"), (5, "32 64", "4"), (8, "15 24", "4"), (9, "15 24", "1"),
+                                          (5, "33 40", "0"), (8, "20 70", "0")])
+def test_tasks_of_8_slices(rules, nz, box, split):
+    """Volumes of at most 8 slices and the small box, at 16-slice runs only."""
+    tiles, voxels = 27, 27 * 27 * 256 * nz
+    line = f"plan p %d {box} 4 {voxels} {tiles} {tiles} {nz} 49 1 1"
+    assert rules(line % 16, "class p")[0][1:] == [split, "0" if split == "1" else "1"]
+    assert rules(line % 8, "class p")[0][1:] == ["0", "1"]

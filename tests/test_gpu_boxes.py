@@ -180,3 +180,29 @@ def test_batch_of_unlike_boxes():
     alone = [K.backproject(p, g) for p, g in big]
     for v, a in zip(K.backproject_batch(*zip(*big)), alone):
         assert torch.equal(v, a)
+
+
+# volumes of at most 8 slices with many tiles, which take tasks of 8 slices, and of 9, which do not
+@pytest.mark.parametrize("nxy,nz", [(440, 1), (300, 4), (300, 8), (300, 9)])
+def test_thin_volumes(nxy, nz):
+    """Against runs of 32 slices, which are never split, as in test_splits; alone, in stages and in a
+    group the bits are the same."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = configs.tiny(nxy=nxy, nz=nz, cols=96, rows=16, views_per_turn=72, turns=4, feed=48.0, dxy=200.0 / nxy,
+                      slices_per_pitch=24)
+    geom, gr = wl.geom.as_dict(), wl.grid.as_dict()
+    print(f"[case] {nxy}^2 x {nz}", flush=True)
+    plan, ref_plan = K.Plan(geom, gr, device=0), K.Plan(geom, gr, device=0, bp_slices=32)
+    torch.manual_seed(0)
+    sino = torch.rand(geom["n_views"], geom["det_rows"], geom["det_cols"], device="cuda")
+    vol, ref = K.recon(plan, sino), K.recon(ref_plan, sino)
+    assert bool(((vol == 0) == (ref == 0)).all())
+    err = float((vol - ref).double().norm() / ref.double().norm())
+    print(f"[parity] {err:.2e}", flush=True)
+    assert err <= 25 * 2.0 ** -24
+    gF = K.filter_views(plan, sino)
+    assert torch.equal(K.backproject(plan, gF), vol)
+    both = torch.full((2, nz, nxy, nxy), float("nan"), device="cuda")
+    K.backproject_batch([plan, plan], [gF, gF], vols=[both[0], both[1]])
+    assert torch.equal(both[0], vol) and torch.equal(both[1], vol)
