@@ -472,7 +472,7 @@ void launch_bpT(const KParams &k, hipStream_t s, const float *gvol, void *gFout,
     };
     if (fb) go(k_bpT_lds<KZ, true, DET, 66, false>);
     else if (shape.pitch == 34) go(k_bpT_lds<KZ, false, DET, 34, false>);
-    else if (shape.pitch == 66 && !bpT_window(k)) go(k_bpT_lds<KZ, false, DET, 66, false>);
+    else if (shape.pitch == 66 && !bpT_window(k, DET)) go(k_bpT_lds<KZ, false, DET, 66, false>);
     else if (shape.pitch == 66) go(k_bpT_lds<KZ, false, DET, 66, true>);
     else go(k_bpT_lds<KZ, false, DET, 0, true>);
 }

@@ -201,13 +201,24 @@ inline int bpT_parts(const KParams &k) {
     return full < 60 ? 32 : (full < 250 ? 16 : (full < 1500 ? 8 : (full < 6000 ? 4 : 2)));
 }
 
-// Whether the rows' sums are kept in a window common to the wave (WIN).  It takes half of the LDS
-// atomics' instructions and fewer operations, but its lanes reach one column's cells together
-// where the slice-by-slice walk has turned their slices against each other, so it pays only where
-// boxes are wide enough to keep the lanes apart: whole adjoint, walk / window, 512^2 x 10 network pitch
-// (boxes 20 x 57) 2.22 / 1.66 ms, 256^2 x 32 (40 x 79) 5.54 / 5.20, 128^2 x 8 (20 x 217) 0.51 / 0.40,
-// clinical (32 x 44) 42.7 / 47.7, 256^2 x 64 sparse (49 x 25) 7.3 / 13.0.
-inline bool bpT_window(const KParams &k) { return k.bp_box_cols > 50; }
+// Whether the rows' sums are kept in a window common to the wave (WIN) in a plan of more than 32 box
+// columns.  It takes half of the LDS atomics' instructions and fewer operations, but its lanes reach one
+// column's cells together where the slice-by-slice walk has turned their slices against each other, so
+// it pays where boxes are wide for their rows, which keeps the lanes apart; always where an update costs
+// more (fixed point: twice the conversions) and in runs of 32 slices, whose walk merges least.  Whole
+// adjoint, walk / window, ms:
+//     16 slices    20 x 36  1.88 / 1.53    20 x 57  1.68 / 1.31    32 x 44  11.1 / 12.3    32 x 51  11.5 / 11.9
+//                  32 x 53  11.7 / 11.8    34 x 43  1.10 / 1.14    40 x 49  4.11 / 4.44    40 x 58  4.38 / 4.54
+//                  40 x 62  4.46 / 4.52    40 x 67  5.49 / 5.19    40 x 79  5.58 / 5.19    53 x 66  9.91 / 9.09
+//     fixed point  20 x 36  2.43 / 1.35    32 x 33  12.5 / 10.8    32 x 44  12.9 / 10.2    34 x 37  1.38 / 1.02
+//                  49 x 39  9.50 / 8.31    40 x 62  5.12 / 4.18    40 x 79  6.49 / 5.34
+//     32 slices    20 x 38  3.52 / 1.94    40 x 43  1.99 / 1.36    55 x 44  16.4 / 14.2    65 x 49  5.88 / 5.01
+//     8 slices     20 x 47  1.74 / 1.55    22 x 49  3.57 / 4.31    18 x 51  10.8 / 11.6    20 x 57  1.31 / 1.10
+// (8 slices: no line through rows and columns separates the two; errors against float64 are the same.)
+inline bool bpT_window(const KParams &k, bool fixed_point) {
+    if (k.bp_box_cols > 64 || fixed_point || k.bp_kz == 32) return true;
+    return k.bp_kz == 8 ? k.bp_box_cols > 50 : 10 * k.bp_box_cols >= 17 * k.bp_box_rows;
+}
 
 }  // namespace bpdev
 }  // namespace kats

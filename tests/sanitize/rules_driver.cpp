@@ -2,7 +2,7 @@
 //   plan NAME kz box_rows box_cols atan_degree valid_voxels tiles_x tiles_y nz slices_per_pitch pitches runs
 //   class NAME            -> shape split poly4
 //   batch NAME NAME ...   -> shape split poly4 of each
-//   adjoint NAME          -> parts window
+//   adjoint NAME          -> parts, window (float sums), window (fixed point)
 //   order tiles_x tiles_y layers least -> "ok" if every layer's order takes each tile once
 #include <iostream>
 #include <map>
@@ -42,7 +42,8 @@ int main() {
             for (const BpClass &c : batch_classes(ks.data(), (int)ks.size())) print(c);
         } else if (what == "adjoint") {
             in >> name;
-            std::cout << bpT_parts(plans.at(name)) << ' ' << bpT_window(plans.at(name));
+            const KParams &k = plans.at(name);
+            std::cout << bpT_parts(k) << ' ' << bpT_window(k, false) << ' ' << bpT_window(k, true);
         } else if (what == "order") {
             unsigned tx, ty, layers, least;
             in >> tx >> ty >> layers >> least;

@@ -87,3 +87,13 @@ def test_tasks_of_8_slices(rules, nz, box, split):
     line = f"plan p %d {box} 4 {voxels} {tiles} {tiles} {nz} 49 1 1"
     assert rules(line % 16, "class p")[0][1:] == [split, "0" if split == "1" else "1"]
     assert rules(line % 8, "class p")[0][1:] == ["0", "1"]
+
+
+# boxes measured on either side of the line, slices a run; whether rows' sums are kept in a window
+@pytest.mark.parametrize("kz,box,window", [
+    (16, "20 36", 1), (16, "20 57", 1), (16, "32 44", 0), (16, "32 51", 0), (16, "32 53", 0), (16, "34 43", 0),
+    (16, "40 49", 0), (16, "40 58", 0), (16, "40 62", 0), (16, "40 67", 1), (16, "53 66", 1), (32, "55 44", 1),
+    (32, "65 49", 1), (8, "22 49", 0), (8, "20 57", 1)])
+def test_adjoint_window(rules, kz, box, window):
+    line = f"plan p {kz} {box} 4 {1 << 21} 16 16 32 49 1 2"
+    assert rules(line, "adjoint p")[0][1:] == [str(window), "1"]
