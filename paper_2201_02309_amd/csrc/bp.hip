@@ -536,7 +536,7 @@ hipError_t launch_backproject_batch(const KParams *ks, const float *const *gF, f
                     if (!(classes[i] == cls)) continue;
                     const long long tasks = (long long)k.bp_tiles_x * k.bp_tiles_y * k.n_pitches * k.bp_runs * kSubs[split];
                     if (tasks == 0) continue;
-                    if (grp.n == kGroupMax || total + tasks > 0x7fffffffLL) flush();
+                    if (grp.n == kGroupMax || total + tasks > kMostThreads / (kNT * kTeams[split])) flush();
                     BpRequest &q = grp.r[grp.n++];
                     q.a = bp_args(k);
                     q.gF = gF[i];

@@ -15,6 +15,9 @@ constexpr int kT = kBpTile;               // 16
 constexpr int kNT = kT * kT;              // lanes of a tile's workgroup
 constexpr unsigned kLdsBytes = 163840;    // per CU and workgroup on gfx950
 
+// Limits of a launch: blocks along z, threads along x (the batches' grids)
+constexpr long long kMostLayers = 65535, kMostThreads = (1ll << 32) - 1;
+
 // Tile of block l (0 .. tiles - 1) of layer z of a launch whose layers (slice runs, pitches, parts)
 // of tiles_x x tiles_y tiles follow one another; first: the launch's block index of the layer's
 // first block.
@@ -126,6 +129,9 @@ inline BpClass kernel_class(const KParams &k) {
     // (the widest shape: 136 floats, 38 rows and more do not fit four times)
     if (kTeams[c.split] > 1 && c.shape < kFallback && bp_bytes(kTeams[c.split], kShapeCols[c.shape] + 8, k.bp_box_rows < 32 ? 32 : k.bp_box_rows, 0) + 64 > kLdsBytes)
         c.split = kHalves;
+    // a split whose tasks would pass a launch's limits is left out (a whole one is as large as ever)
+    const long long all = (long long)k.n_pitches * k.bp_runs * kSubs[c.split];
+    if (all > kMostLayers || all * k.bp_tiles_x * k.bp_tiles_y > kMostThreads / (kNT * kTeams[c.split])) c.split = kWhole;
     if (c.split == kWhole && c.shape == 0 && std::min(k.ns, k.nz) <= 8) c.split = kThin;
     if (c.split != kWhole && c.split != kThin) c.poly4 = 0;    // one instance each: the longer polynomial's further terms are 0
     return c;
@@ -198,7 +204,9 @@ inline std::vector<BpClass> batch_classes(const KParams *ks, int n) {
 //   8192 (512^2 x 128)         42916 / 42898 (42589 in 2) / 43636
 inline int bpT_parts(const KParams &k) {
     const long long full = k.n_valid / ((long long)kT * kT * 16);
-    return full < 60 ? 32 : (full < 250 ? 16 : (full < 1500 ? 8 : (full < 6000 ? 4 : 2)));
+    const long long parts = full < 60 ? 32 : (full < 250 ? 16 : (full < 1500 ? 8 : (full < 6000 ? 4 : 2)));
+    const long long most = kMostLayers / std::max(1ll, (long long)k.n_pitches * k.bp_runs);
+    return (int)std::max(1ll, std::min(parts, most));
 }
 
 // Whether the rows' sums are kept in a window common to the wave (WIN) in a plan of more than 32 box

@@ -97,3 +97,19 @@ def test_tasks_of_8_slices(rules, nz, box, split):
 def test_adjoint_window(rules, kz, box, window):
     line = f"plan p {kz} {box} 4 {1 << 21} 16 16 32 49 1 2"
     assert rules(line, "adjoint p")[0][1:] == [str(window), "1"]
+
+
+@pytest.mark.parametrize("pitches,split,parts", [(200, "3", 32), (2047, "3", 32), (2048, "3", 31), (16383, "3", 4),
+                                                 (16384, "4", 3), (65535, "4", 1), (70000, "4", 1)])
+def test_tall_volumes(rules, pitches, split, parts):
+    """Layers times the tasks or parts of each stay within 65535 where the layers alone do."""
+    line = f"plan p 16 12 14 4 {16 * pitches // 4} 1 1 {pitches} 1 {pitches} 1"
+    out = rules(line, "class p", "adjoint p")
+    assert out[0][1] == split and int(out[1][0]) == parts
+
+
+def test_wide_volumes(rules):
+    """Tasks times the threads of each stay below 2^32."""
+    for tiles, split in ((1023, "3"), (1025, "0")):
+        line = f"plan p 16 12 80 4 4096 {tiles} {tiles} 3 3 1 1"
+        assert rules(line, "class p")[0][1] == split
