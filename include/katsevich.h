@@ -56,7 +56,7 @@ enum {
     KATS_EWORKSPACE = -4,        /* workspace smaller than katsevich_plan_info says */
     KATS_ENOTBOUND = -5,         /* compute call on a plan without device tables */
     KATS_EHIP = -6,              /* a HIP runtime call or kernel launch failed */
-    KATS_ENOMEM = -7             /* host allocation failed while planning */
+    KATS_ENOMEM = -7             /* a host allocation failed */
 };
 
 /* Scan geometry (Sec. II helix, Sec. III-C detector coordinates).  R: source radius;
@@ -256,7 +256,7 @@ int katsevich_backproject(katsevich_plan_t plan, const float *d_gF, float *d_vol
  * is split in another way, are grouped apart (see bp_box_rows / bp_box_cols of katsevich_plan_info).  All plans
  * must be bound and use the same bp_slices.  No device memory besides the arrays named;
  * the host arrays may be reused when the call returns.  Asynchronous on stream.
- * Errors: KATS_EINVAL, KATS_ENOTBOUND, KATS_EHIP. */
+ * Errors: KATS_EINVAL, KATS_ENOTBOUND, KATS_ENOMEM, KATS_EHIP. */
 int katsevich_backproject_batch(const katsevich_plan_t *plans, const float *const *d_gF,
                                 float *const *d_vol, int n, void *stream);
 

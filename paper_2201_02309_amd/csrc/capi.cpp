@@ -718,22 +718,26 @@ int katsevich_backproject_batch(const katsevich_plan_t *plans, const float *cons
     g_err.clear();
     if (!plans || !d_gF || !d_vol || n < 1)
         return fail(KATS_EINVAL, "katsevich_backproject_batch: null argument or n < 1");
-    std::vector<kats::KParams> ks((size_t)n);
-    int kz = -1;
-    for (int i = 0; i < n; ++i) {
-        if (!plans[i] || !d_gF[i] || !d_vol[i])
-            return fail(KATS_EINVAL, "katsevich_backproject_batch: null plan or buffer at item " + std::to_string(i));
-        if (!plans[i]->P.d_tables)
-            return fail(KATS_ENOTBOUND, "katsevich_backproject_batch: plan " + std::to_string(i) + " not bound");
-        if (kz < 0) kz = plans[i]->P.bp_kz;
-        if (plans[i]->P.bp_kz != kz)
-            return fail(KATS_EINVAL, "katsevich_backproject_batch: plans use different bp_slices");
-        ks[(size_t)i] = kats::make_params(plans[i]->P);
+    try {
+        std::vector<kats::KParams> ks((size_t)n);
+        int kz = -1;
+        for (int i = 0; i < n; ++i) {
+            if (!plans[i] || !d_gF[i] || !d_vol[i])
+                return fail(KATS_EINVAL, "katsevich_backproject_batch: null plan or buffer at item " + std::to_string(i));
+            if (!plans[i]->P.d_tables)
+                return fail(KATS_ENOTBOUND, "katsevich_backproject_batch: plan " + std::to_string(i) + " not bound");
+            if (kz < 0) kz = plans[i]->P.bp_kz;
+            if (plans[i]->P.bp_kz != kz)
+                return fail(KATS_EINVAL, "katsevich_backproject_batch: plans use different bp_slices");
+            ks[(size_t)i] = kats::make_params(plans[i]->P);
+        }
+        hipError_t e = kats::launch_backproject_batch(ks.data(), d_gF, d_vol, n, kz,
+                                                      static_cast<hipStream_t>(stream));
+        if (e != hipSuccess) return hip_fail(e, "katsevich_backproject_batch: launch");
+        return KATS_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(KATS_ENOMEM, "katsevich_backproject_batch: out of host memory");
     }
-    hipError_t e = kats::launch_backproject_batch(ks.data(), d_gF, d_vol, n, kz,
-                                                  static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return hip_fail(e, "katsevich_backproject_batch: launch");
-    return KATS_OK;
 }
 
 void katsevich_plan_destroy(katsevich_plan_t plan) { delete plan; }

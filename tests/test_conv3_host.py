@@ -1,4 +1,4 @@
-"""Host checks of the network kernels' entry points: which shapes and strides they take.  Without a GPU
+"""Host checks of the network kernels' and the batch's entry points: what they take.  Without a GPU
 an accepted call ends at its launch (KATS_EHIP); the buffers are never touched."""
 from ctypes import c_int64, c_uint64, c_void_p
 
@@ -71,3 +71,18 @@ def test_launch_limits_of_prelu(shape, ok):
                                       ((1, 1, 1, 4 * 65535, 1, 1), True), ((1, 1, 1, 4 * 65535 + 1, 1, 1), False)])
 def test_launch_limits_of_convolutions(shape, ok):
     assert _conv(shape, (1, 1, 1), (1, 1, 1)) == (EHIP if ok else EINVAL)
+
+
+def test_batch_without_host_memory():
+    """A batch whose host tables cannot be allocated is refused, not ended by an exception."""
+    import subprocess
+    import sys
+    code = """
+import ctypes, resource, sys
+lib = ctypes.CDLL(sys.argv[1])
+resource.setrlimit(resource.RLIMIT_AS, (16 << 30, 16 << 30))
+p = (ctypes.c_void_p * 1)(1 << 20)
+print(lib.katsevich_backproject_batch(p, p, p, (1 << 31) - 1, None))
+"""
+    r = subprocess.run([sys.executable, "-c", code, K.katsevich.LIB_PATH], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.split() == ["-7"], (r.returncode, r.stderr[-500:])
