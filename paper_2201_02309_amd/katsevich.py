@@ -537,13 +537,35 @@ def dense_volume(t):
     return t if near and rows_dense(t) else t.contiguous()
 
 
+def _volume(t, name, like=None):
+    """t, a float32 GPU volume [B, C, D, H, W] with dense planes; like: one of equal size (the channels
+    apart) and device."""
+    import torch
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.dim() == 5
+            and rows_dense(t)):
+        raise KatsevichError(-1, f"{name}: expected a float32 CUDA tensor [B, C, D, H, W] with dense planes")
+    if like is not None and (t.shape[:1] + t.shape[2:] != like.shape[:1] + like.shape[2:] or t.device != like.device):
+        raise KatsevichError(-3, f"{name}: {tuple(t.shape)} on {t.device} against {tuple(like.shape)} on {like.device}")
+    return t
+
+
+def _parameter(t, shape, like, name):
+    """t, a contiguous float32 tensor of this shape on like's device."""
+    _f32(t, name)
+    if tuple(t.shape) != tuple(shape) or t.device != like.device:
+        raise KatsevichError(-3, f"{name}: {tuple(t.shape)} on {t.device} != {tuple(shape)} on {like.device}")
+
+
 def conv3(x, w, bias=None, transposed=False):
     """katsevich_conv3: 3x3x3 convolution (zero padding 1) of x [B, cin, D, H, W] with w [cout, cin,
     3, 3, 3], or with `transposed` its gradient with respect to the input, w [cin, cout, 3, 3, 3].
     The result is stored as [B, D, cout, H, W].  x: float32, strides as of dense_volume."""
     import torch
-    B, cin, D, H, W = x.shape
+    B, cin, D, H, W = _volume(x, "x").shape
     cout = w.shape[1 if transposed else 0]
+    _parameter(w, (cin, cout, 3, 3, 3) if transposed else (cout, cin, 3, 3, 3), x, "w")
+    if bias is not None:
+        _parameter(bias, (cout,), x, "bias")
     y = torch.empty((B, D, cout, H, W), dtype=torch.float32, device=x.device).permute(0, 2, 1, 3, 4)
     lib = load_library()
     with torch.cuda.device(x.device):
@@ -558,7 +580,10 @@ def conv3_grad(x, dy, weight_shape):
     """katsevich_conv3_grad: gradients (dw, db) of a 3x3x3 convolution from its input and the
     gradient of its output."""
     import torch
-    B, cin, D, H, W = x.shape
+    B, cin, D, H, W = _volume(x, "x").shape
+    _volume(dy, "dy", x)
+    if tuple(weight_shape) != (dy.shape[1], cin, 3, 3, 3):
+        raise KatsevichError(-3, f"weight_shape {tuple(weight_shape)} != {(dy.shape[1], cin, 3, 3, 3)}")
     lib = load_library()
     with torch.cuda.device(x.device):
         dw = torch.empty(weight_shape, dtype=torch.float32, device=x.device)
@@ -575,7 +600,7 @@ def stack3(x):
     """katsevich_stack3: x [B, C, D, H, W] -> [B D, 3 C, H, W], the three depth-shifted copies of x as
     channels.  x: float32, planes dense."""
     import torch
-    B, C, D, H, W = x.shape
+    B, C, D, H, W = _volume(x, "x").shape
     out = torch.empty((B * D, 3 * C, H, W), dtype=torch.float32, device=x.device)
     lib = load_library()
     with torch.cuda.device(x.device):
@@ -588,7 +613,10 @@ def prelu_grad(x, dy, slope):
     """katsevich_prelu_grad: (dx, dslope) of a PReLU with one slope per channel; dx is stored as
     [B, D, C, H, W]."""
     import torch
-    B, C, D, H, W = x.shape
+    B, C, D, H, W = _volume(x, "x").shape
+    _parameter(slope, _volume(dy, "dy", x).shape[1:2], x, "slope")
+    if C != dy.shape[1]:
+        raise KatsevichError(-3, f"dy: {dy.shape[1]} channels != {C}")
     lib = load_library()
     with torch.cuda.device(x.device):
         dx = torch.empty((B, D, C, H, W), dtype=torch.float32, device=x.device).permute(0, 2, 1, 3, 4)

@@ -86,3 +86,15 @@ print(lib.katsevich_backproject_batch(p, p, p, (1 << 31) - 1, None))
 """
     r = subprocess.run([sys.executable, "-c", code, K.katsevich.LIB_PATH], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.split() == ["-7"], (r.returncode, r.stderr[-500:])
+
+
+@pytest.mark.parametrize("call", [lambda x: K.katsevich.conv3(x, torch.zeros(1, 1, 3, 3, 3)),
+                                  lambda x: K.katsevich.conv3_grad(x, x, (1, 1, 3, 3, 3)),
+                                  lambda x: K.katsevich.stack3(x),
+                                  lambda x: K.katsevich.prelu_grad(x, x, torch.zeros(1))])
+def test_volumes_of_another_kind(call):
+    """Host tensors, and types and ranks that the kernels do not read, are refused by the binding."""
+    for x in (torch.zeros(1, 1, 2, 3, 4), torch.zeros(1, 1, 2, 3, 4, dtype=torch.float16), torch.zeros(1, 2, 3, 4)):
+        with pytest.raises(K.KatsevichError) as e:
+            call(x)
+        assert e.value.status == EINVAL
