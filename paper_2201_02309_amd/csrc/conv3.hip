@@ -292,6 +292,7 @@ __global__ __launch_bounds__(kCT) void k_conv3_wsum(const float *__restrict__ pa
 #pragma unroll 8
         for (int p = g; p < np; p += 16) s += (double)part[(size_t)p * kConv3Part + e];
     } else {
+#pragma unroll 8
         for (int p = g; p < np; p += 16) {
             const float *h = part + (size_t)p * kConv3Part + e;
             s += __hiloint2double(__float_as_int(h[0]), __float_as_int(h[16]));
