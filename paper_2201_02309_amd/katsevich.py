@@ -523,45 +523,39 @@ def _volume_strides(t):
     return (c_int64 * 3)(*t.stride()[:3])
 
 
-def rows_dense(t):
-    """Whether every [H, W] plane of t is stored densely, as the convolution calls need."""
-    H, W = t.shape[-2:]
-    return (W == 1 or t.stride(-1) == 1) and (H == 1 or t.stride(-2) == W)
-
-
 def dense_volume(t):
-    """t itself where katsevich_conv3 and katsevich_conv3_grad take its strides (planes stored densely,
+    """t [B, C, D, H, W] itself where the convolution calls take its strides (planes stored densely,
     channels at most 2^30 floats apart), otherwise a dense copy of it."""
-    H, W = t.shape[-2:]
-    near = (t.shape[1] - 1) * t.stride(1) + H * W <= 1 << 30
-    return t if near and rows_dense(t) else t.contiguous()
+    (_, C, _, H, W), (_, sc, _, sh, sw) = t.shape, t.stride()
+    dense = (sw == 1 or W == 1) and (sh == W or H == 1) and (C - 1) * sc + H * W <= 1 << 30
+    return t if dense else t.contiguous()
 
 
 def _volume(t, name, like=None):
-    """t, a float32 GPU volume [B, C, D, H, W] with dense planes; like: one of equal size (the channels
+    """t, a float32 GPU volume [B, C, D, H, W], as dense_volume; like: one of equal size (the channels
     apart) and device."""
     import torch
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.dim() == 5
-            and rows_dense(t)):
-        raise KatsevichError(-1, f"{name}: expected a float32 CUDA tensor [B, C, D, H, W] with dense planes")
-    if like is not None and (t.shape[:1] + t.shape[2:] != like.shape[:1] + like.shape[2:] or t.device != like.device):
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.dim() == 5):
+        raise KatsevichError(-1, f"{name}: expected a float32 CUDA tensor [B, C, D, H, W]")
+    if like is not None and (t.shape[2:] != like.shape[2:] or t.shape[0] != like.shape[0] or t.device != like.device):
         raise KatsevichError(-3, f"{name}: {tuple(t.shape)} on {t.device} against {tuple(like.shape)} on {like.device}")
-    return t
+    return dense_volume(t)
 
 
 def _parameter(t, shape, like, name):
     """t, a contiguous float32 tensor of this shape on like's device."""
     _f32(t, name)
-    if tuple(t.shape) != tuple(shape) or t.device != like.device:
+    if t.shape != shape or t.device != like.device:
         raise KatsevichError(-3, f"{name}: {tuple(t.shape)} on {t.device} != {tuple(shape)} on {like.device}")
 
 
 def conv3(x, w, bias=None, transposed=False):
     """katsevich_conv3: 3x3x3 convolution (zero padding 1) of x [B, cin, D, H, W] with w [cout, cin,
     3, 3, 3], or with `transposed` its gradient with respect to the input, w [cin, cout, 3, 3, 3].
-    The result is stored as [B, D, cout, H, W].  x: float32, strides as of dense_volume."""
+    The result is stored as [B, D, cout, H, W]."""
     import torch
-    B, cin, D, H, W = _volume(x, "x").shape
+    x = _volume(x, "x")
+    B, cin, D, H, W = x.shape
     cout = w.shape[1 if transposed else 0]
     _parameter(w, (cin, cout, 3, 3, 3) if transposed else (cout, cin, 3, 3, 3), x, "w")
     if bias is not None:
@@ -580,8 +574,9 @@ def conv3_grad(x, dy, weight_shape):
     """katsevich_conv3_grad: gradients (dw, db) of a 3x3x3 convolution from its input and the
     gradient of its output."""
     import torch
-    B, cin, D, H, W = _volume(x, "x").shape
-    _volume(dy, "dy", x)
+    x = _volume(x, "x")
+    dy = _volume(dy, "dy", x)
+    B, cin, D, H, W = x.shape
     if tuple(weight_shape) != (dy.shape[1], cin, 3, 3, 3):
         raise KatsevichError(-3, f"weight_shape {tuple(weight_shape)} != {(dy.shape[1], cin, 3, 3, 3)}")
     lib = load_library()
@@ -598,9 +593,10 @@ def conv3_grad(x, dy, weight_shape):
 
 def stack3(x):
     """katsevich_stack3: x [B, C, D, H, W] -> [B D, 3 C, H, W], the three depth-shifted copies of x as
-    channels.  x: float32, planes dense."""
+    channels."""
     import torch
-    B, C, D, H, W = _volume(x, "x").shape
+    x = _volume(x, "x")
+    B, C, D, H, W = x.shape
     out = torch.empty((B * D, 3 * C, H, W), dtype=torch.float32, device=x.device)
     lib = load_library()
     with torch.cuda.device(x.device):
@@ -613,10 +609,12 @@ def prelu_grad(x, dy, slope):
     """katsevich_prelu_grad: (dx, dslope) of a PReLU with one slope per channel; dx is stored as
     [B, D, C, H, W]."""
     import torch
-    B, C, D, H, W = _volume(x, "x").shape
-    _parameter(slope, _volume(dy, "dy", x).shape[1:2], x, "slope")
-    if C != dy.shape[1]:
+    x = _volume(x, "x")
+    dy = _volume(dy, "dy", x)
+    B, C, D, H, W = x.shape
+    if dy.shape[1] != C:
         raise KatsevichError(-3, f"dy: {dy.shape[1]} channels != {C}")
+    _parameter(slope, (C,), x, "slope")
     lib = load_library()
     with torch.cuda.device(x.device):
         dx = torch.empty((B, D, C, H, W), dtype=torch.float32, device=x.device).permute(0, 2, 1, 3, 4)

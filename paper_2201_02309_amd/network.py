@@ -54,11 +54,12 @@ def _plain(*tensors):
         if type(t) not in (torch.Tensor, nn.Parameter) or t.dtype != torch.float32 or not t.is_cuda \
                 or t.device != tensors[0].device or not torch._C._has_storage(t):
             return False
-    return not (torch.is_autocast_enabled("cuda") or torch.jit.is_tracing()
+    return not (torch.is_autocast_enabled("cuda") or torch._C._is_tracing()
                 or torch.autograd.forward_ad._current_level >= 0
                 or torch._C._functorch.peek_interpreter_stack() is not None
                 or torch._C._len_torch_dispatch_stack() > 0
-                or any(not isinstance(m, DeviceContext) for m in _get_current_function_mode_stack()))
+                or torch._C._len_torch_function_stack() > 0 and any(
+                    not isinstance(m, DeviceContext) for m in _get_current_function_mode_stack()))
 
 
 def _native_volume(x, channels):
@@ -84,8 +85,9 @@ def _check_kept(gy, *kept):
     """Hooks on saved tensors may hand back others than were kept, which torch's operators refuse and
     the kernels would read out of range: every (tensor, shape) must have that shape and gy's type and
     device."""
+    dtype, device = gy.dtype, gy.device
     for t, shape in kept:
-        if t.dtype != gy.dtype or t.device != gy.device or t.shape != torch.Size(shape):
+        if t.shape != shape or t.dtype != dtype or t.device != device:
             raise RuntimeError(f"a saved tensor came back as {t.dtype} {tuple(t.shape)} on {t.device}: "
                                f"{gy.dtype} {tuple(shape)} on {gy.device} was kept")
 
@@ -102,7 +104,7 @@ class _Conv3Fn(torch.autograd.Function):
         # (x plays a part in the weight's gradient alone: a frozen layer's may change)
         ctx.save_for_backward(x if ctx.needs_input_grad[1] else None, weight)
         ctx.shape = x.shape
-        stack = _K.stack3(x if _K.rows_dense(x) else x.contiguous())
+        stack = _K.stack3(x)
         return _conv_stack(stack, x.shape[0], x.shape[2], weight, bias)
 
     @staticmethod
@@ -113,7 +115,7 @@ class _Conv3Fn(torch.autograd.Function):
         want = ctx.needs_input_grad
         again = torch.is_grad_enabled()
         _check_kept(gy, (x, ctx.shape), (weight, (gy.shape[1], ctx.shape[1], 3, 3, 3)))
-        if again or not _plain(x, weight) or not _native_conv(gy, weight.transpose(0, 1), x.new_empty(x.shape[1])):
+        if again or not _plain(gy, x, weight) or not _native_volume(gy, gy.shape[1]):
             with torch.enable_grad():
                 bias = weight.new_zeros(weight.shape[0], requires_grad=True)   # its value plays no part
                 args = [t if t.requires_grad else t.detach().requires_grad_(n)
@@ -125,7 +127,7 @@ class _Conv3Fn(torch.autograd.Function):
         gx = _K.conv3(gy, weight.contiguous(), transposed=True) if want[0] else None
         gw = gb = None
         if want[1] or want[2]:
-            gw, gb = _K.conv3_grad(_K.dense_volume(x), gy, tuple(weight.shape))
+            gw, gb = _K.conv3_grad(x, gy, tuple(weight.shape))
         return gx, gw if want[1] else None, gb if want[2] else None
 
 
@@ -155,7 +157,7 @@ class Conv3x3x3(nn.Module):
             return _conv3x3x3(x, w, b)
         if torch.is_grad_enabled() and (x.requires_grad or w.requires_grad or b.requires_grad):
             return _Conv3Fn.apply(x.clone() if self.copy_input and w.requires_grad else x, w.clone(), b)
-        return _K.conv3(_K.dense_volume(x), w.contiguous(), b.contiguous())
+        return _K.conv3(x, w.contiguous(), b.contiguous())
 
 
 class _PReLUFn(torch.autograd.Function):
@@ -179,8 +181,7 @@ class _PReLUFn(torch.autograd.Function):
                 grads = iter(torch.autograd.grad(F.prelu(*args), [t for t, n in zip(args, want) if n], gy,
                                                  create_graph=again))
             return tuple(next(grads) if n else None for n in want)
-        gx, gw = _K.prelu_grad(x if _K.rows_dense(x) else x.contiguous(),
-                               gy if _K.rows_dense(gy) else gy.contiguous(), weight.contiguous())
+        gx, gw = _K.prelu_grad(x, gy, weight.contiguous())
         return gx if want[0] else None, gw if want[1] else None
 
 
