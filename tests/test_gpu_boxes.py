@@ -107,8 +107,8 @@ def test_adjoint_of_values_that_are_not_finite(bad):
     assert np.allclose(got[~seen], base[~seen], atol=1e-5 * np.abs(base).max())
 
 
-# tiles of a layer: 528 = 16 * 33 and 567 (ragged rows), where the forward's order by XCD begins, and
-# 1023, 1056, 1089 around the adjoint's; slices of one and of two layers
+# tiles of a layer: 528 = 16 * 33 and 567 (ragged rows), in plain order, and 1023, 1056, 1089 around the
+# least of the adjoint's order by XCD; slices of one and of two layers
 @pytest.mark.parametrize("nx,ny,nz", [(520, 256, 5), (330, 432, 20), (528, 490, 5), (513, 505, 5), (520, 513, 18)])
 def test_tile_order(nx, ny, nz):
     """Many tiles, in whatever order their blocks take them, against the same voxels in grids of few
@@ -235,3 +235,9 @@ def test_many_pitches():
     assert bool((vol != 0).any(dim=(1, 2))[1:-1].all())
     assert float((vol - ref).double().norm() / ref.double().norm()) <= 2e-5
     assert float((gsino - gref).norm() / gref.norm()) <= 2e-5 + 2.0 ** -22 * plan.info["bp_box_cols"]
+
+
+# 767, 768 and 783 tiles a layer, ragged rows and columns: around the least of the forward's order by XCD
+@pytest.mark.parametrize("nx,ny,nz", [(201, 939, 3), (384, 512, 3), (425, 460, 18)])
+def test_tile_order_of_the_forward(nx, ny, nz):
+    test_tile_order(nx, ny, nz)
