@@ -32,7 +32,7 @@ constexpr long long kMostLayers = 65535, kMostThreads = (1ll << 32) - 1;
 // reconstruction 10.46 -> 10.08 ms, whole adjoint 42.5 -> 41.8 ms; 512 x 512 x 10 (network), forward and
 // adjoint 2.25 -> 1.90 ms.  Smaller layers read little, and their fewer blocks show what balance is
 // lost.  Plain order / this one by tiles, ms:
-//   forward   529, one layer (356^2 x 5): 0.340 / 0.354   256: 4.52 / 4.48   361 (301^2 x 77): 3.00 / 3.04   400: 4.87 / 4.83   576: 3.80 / 3.74
+//   forward   529, one layer (356^2 x 5): 0.329 / 0.336   256: 4.52 / 4.48   361 (301^2 x 77): 3.00 / 3.04   400: 4.87 / 4.83   576: 3.80 / 3.74
 //             784: 4.90 / 4.75   1024 (512^2 x 32): 3.29 / 3.20
 //   adjoint   256 (sparse): 18.70 / 18.95   400: 14.74 / 14.70   576: 12.88 / 12.98   784: 16.41 / 16.57
 //             1024: 11.68 / 11.15
