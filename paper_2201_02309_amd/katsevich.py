@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from contextlib import nullcontext
 from ctypes import POINTER, byref, c_double, c_int, c_int32, c_int64, c_uint64, c_void_p, c_char_p
 
 import numpy as np
@@ -531,11 +532,25 @@ def dense_volume(t):
     return t if dense else t.contiguous()
 
 
+def _on(device):
+    """A context in which this device is the current one; entering torch's own costs as much host time
+    as a launch where it already is."""
+    import torch
+    return nullcontext() if torch.cuda.current_device() == device.index else torch.cuda.device(device)
+
+
+def _gpu_f32(t):
+    """Whether t is a float32 GPU tensor (float32 is the one floating type of 4 bytes)."""
+    if not getattr(t, "is_cuda", False):
+        return False
+    dtype = t.dtype
+    return dtype.is_floating_point and dtype.itemsize == 4
+
+
 def _volume(t, name, like=None):
     """t, a float32 GPU volume [B, C, D, H, W], as dense_volume; like: one of equal size (the channels
     apart) and device."""
-    import torch
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.dim() == 5):
+    if not _gpu_f32(t) or t.dim() != 5:
         raise KatsevichError(-1, f"{name}: expected a float32 CUDA tensor [B, C, D, H, W]")
     if like is not None and (t.shape[2:] != like.shape[2:] or t.shape[0] != like.shape[0] or t.device != like.device):
         raise KatsevichError(-3, f"{name}: {tuple(t.shape)} on {t.device} against {tuple(like.shape)} on {like.device}")
@@ -543,10 +558,12 @@ def _volume(t, name, like=None):
 
 
 def _parameter(t, shape, like, name):
-    """t, a contiguous float32 tensor of this shape on like's device."""
-    _f32(t, name)
+    """t, a float32 tensor of this shape on like's device, contiguous."""
+    if not _gpu_f32(t):
+        raise KatsevichError(-1, f"{name}: expected a float32 CUDA tensor")
     if t.shape != shape or t.device != like.device:
         raise KatsevichError(-3, f"{name}: {tuple(t.shape)} on {t.device} != {tuple(shape)} on {like.device}")
+    return t.contiguous()
 
 
 def conv3(x, w, bias=None, transposed=False):
@@ -557,12 +574,12 @@ def conv3(x, w, bias=None, transposed=False):
     x = _volume(x, "x")
     B, cin, D, H, W = x.shape
     cout = w.shape[1 if transposed else 0]
-    _parameter(w, (cin, cout, 3, 3, 3) if transposed else (cout, cin, 3, 3, 3), x, "w")
+    w = _parameter(w, (cin, cout, 3, 3, 3) if transposed else (cout, cin, 3, 3, 3), x, "w")
     if bias is not None:
-        _parameter(bias, (cout,), x, "bias")
+        bias = _parameter(bias, (cout,), x, "bias")
     y = torch.empty((B, D, cout, H, W), dtype=torch.float32, device=x.device).permute(0, 2, 1, 3, 4)
     lib = load_library()
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(lib, lib.katsevich_conv3(
             c_void_p(x.data_ptr()), _volume_strides(x), c_void_p(w.data_ptr()),
             c_void_p(0 if bias is None else bias.data_ptr()), c_void_p(y.data_ptr()), _volume_strides(y),
@@ -580,7 +597,7 @@ def conv3_grad(x, dy, weight_shape):
     if tuple(weight_shape) != (dy.shape[1], cin, 3, 3, 3):
         raise KatsevichError(-3, f"weight_shape {tuple(weight_shape)} != {(dy.shape[1], cin, 3, 3, 3)}")
     lib = load_library()
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         dw = torch.empty(weight_shape, dtype=torch.float32, device=x.device)
         db = torch.empty(weight_shape[0], dtype=torch.float32, device=x.device)
         part = torch.empty(int(lib.katsevich_conv3_scratch_bytes()), dtype=torch.uint8, device=x.device)
@@ -599,7 +616,7 @@ def stack3(x):
     B, C, D, H, W = x.shape
     out = torch.empty((B * D, 3 * C, H, W), dtype=torch.float32, device=x.device)
     lib = load_library()
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(lib, lib.katsevich_stack3(c_void_p(x.data_ptr()), _volume_strides(x), c_void_p(out.data_ptr()),
                                          (c_int64 * 5)(B, C, D, H, W), _stream_handle(x.device)))
     return out
@@ -614,9 +631,9 @@ def prelu_grad(x, dy, slope):
     B, C, D, H, W = x.shape
     if dy.shape[1] != C:
         raise KatsevichError(-3, f"dy: {dy.shape[1]} channels != {C}")
-    _parameter(slope, (C,), x, "slope")
+    slope = _parameter(slope, (C,), x, "slope")
     lib = load_library()
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         dx = torch.empty((B, D, C, H, W), dtype=torch.float32, device=x.device).permute(0, 2, 1, 3, 4)
         dslope = torch.empty(C, dtype=torch.float32, device=x.device)
         shape = (c_int64 * 5)(B, C, D, H, W)

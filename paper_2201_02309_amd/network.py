@@ -77,8 +77,8 @@ def _native_conv(x, weight, bias):
     if not _plain(x, weight, bias) or x.dim() != 5:     # (a symbolic x has no dim() to compare)
         return False
     cin, cout = x.shape[1], weight.shape[0]
-    return (1 <= cout <= 16 and cin <= 16 and tuple(weight.shape) == (cout, cin, 3, 3, 3)
-            and tuple(bias.shape) == (cout,) and _native_volume(x, cin))
+    return (1 <= cout <= 16 and cin <= 16 and weight.shape == (cout, cin, 3, 3, 3)
+            and bias.shape == (cout,) and _native_volume(x, cin))
 
 
 def _check_kept(gy, *kept):
@@ -124,7 +124,7 @@ class _Conv3Fn(torch.autograd.Function):
                                                  gy, create_graph=again))
             return tuple(next(grads) if n else None for n in want)
         gy = _K.dense_volume(gy)
-        gx = _K.conv3(gy, weight.contiguous(), transposed=True) if want[0] else None
+        gx = _K.conv3(gy, weight, transposed=True) if want[0] else None
         gw = gb = None
         if want[1] or want[2]:
             gw, gb = _K.conv3_grad(x, gy, tuple(weight.shape))
@@ -157,7 +157,7 @@ class Conv3x3x3(nn.Module):
             return _conv3x3x3(x, w, b)
         if torch.is_grad_enabled() and (x.requires_grad or w.requires_grad or b.requires_grad):
             return _Conv3Fn.apply(x.clone() if self.copy_input and w.requires_grad else x, w.clone(), b)
-        return _K.conv3(x, w.contiguous(), b.contiguous())
+        return _K.conv3(x, w, b)
 
 
 class _PReLUFn(torch.autograd.Function):
@@ -181,7 +181,7 @@ class _PReLUFn(torch.autograd.Function):
                 grads = iter(torch.autograd.grad(F.prelu(*args), [t for t, n in zip(args, want) if n], gy,
                                                  create_graph=again))
             return tuple(next(grads) if n else None for n in want)
-        gx, gw = _K.prelu_grad(x, gy, weight.contiguous())
+        gx, gw = _K.prelu_grad(x, gy, weight)
         return gx if want[0] else None, gw if want[1] else None
 
 
